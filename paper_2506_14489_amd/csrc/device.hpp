@@ -143,6 +143,35 @@ struct PermTE02 {
                                                int i) const {
         return xor3(at(w0, off0, 0), at(w2, off2, 2), rotl8(xor3(at(w1, off0, 1), at(w3, off2, 3), K.rot(i))));
     }
+    // A round of two blocks whose inputs differ in bit 0 of w[0] only: of the
+    // 16 lookups one differs (byte 0 of w[0], row x ^ 1), and it enters column
+    // 0 only.  c: block 0's columns; the return value is block 1's column 0.
+    template <typename Key>
+    __device__ __forceinline__ uint32_t first_round_pair(const uint32_t (&w)[4], const Key &K, uint32_t (&c)[4]) const {
+        const uint32_t p = __builtin_amdgcn_perm(w[0], off0, 0x0c0c0400u);
+        const uint32_t a = lds_read(p), a1 = lds_read(p ^ kTableRowBytes);
+        c[0] = xor3(a, at(w[2], off2, 2), rotl8(xor3(at(w[1], off0, 1), at(w[3], off2, 3), K.rot(4))));
+        c[1] = column(w[1], w[2], w[3], w[0], K, 5);
+        c[2] = column(w[2], w[3], w[0], w[1], K, 6);
+        c[3] = column(w[3], w[0], w[1], w[2], K, 7);
+        return xor3(c[0], a, a1);
+    }
+    // A round of two blocks that differ in column 0 only (c[0] and c01): each
+    // new column takes one byte of it, so block 1 replaces 4 of the 16 lookups.
+    template <typename Key>
+    __device__ __forceinline__ void second_round_pair(const uint32_t (&c)[4], uint32_t c01, const Key &K,
+                                                      uint32_t (&d)[4], uint32_t (&d1)[4]) const {
+        const uint32_t a0 = at(c[0], off0, 0), b0 = at(c[0], off0, 1), e0 = at(c[0], off2, 2), f0 = at(c[0], off2, 3);
+        const uint32_t a1 = at(c01, off0, 0), b1 = at(c01, off0, 1), e1 = at(c01, off2, 2), f1 = at(c01, off2, 3);
+        d[0] = xor3(a0, at(c[2], off2, 2), rotl8(xor3(at(c[1], off0, 1), at(c[3], off2, 3), K.rot(8))));
+        d[1] = xor3(at(c[1], off0, 0), at(c[3], off2, 2), rotl8(xor3(at(c[2], off0, 1), f0, K.rot(9))));
+        d[2] = xor3(at(c[2], off0, 0), e0, rotl8(xor3(at(c[3], off0, 1), at(c[1], off2, 3), K.rot(10))));
+        d[3] = xor3(at(c[3], off0, 0), at(c[1], off2, 2), rotl8(xor3(b0, at(c[2], off2, 3), K.rot(11))));
+        d1[0] = xor3(d[0], a0, a1);
+        d1[1] = d[1] ^ rotl8(f0 ^ f1);
+        d1[2] = xor3(d[2], e0, e1);
+        d1[3] = d[3] ^ rotl8(b0 ^ b1);
+    }
     template <typename Key>
     __device__ __forceinline__ uint32_t last_column(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, const Key &K,
                                                     int i) const {
@@ -704,6 +733,160 @@ __device__ __forceinline__ void hash_fraction_n(const Tab &T, const Key &rk, uin
             V[j][4 * h + 3] = s[2 * j + h][3] ^ y3 ^ y1 ^ gid;
         }
     }
+}
+
+// The two-block hashes of NG gates, the AES blocks of all of them round by
+// round.  x: the folded input label that the gates share, gate j under tweak
+// tau + j; V[j] receives the 256-bit fraction: limbs 0-3 are the output words
+// of block 0, 4-7 of block 1.
+//
+// The two blocks of a hash differ in bit 0 of word 0 alone (4 tau and 4 tau +
+// 1), so they share 15 of the 16 lookups of round 1 and 12 of round 2.  Pads
+// are the leading digits of the fraction: limbs 0-2 only ever decide a digit
+// through a carry (see pad_words_top), and without `all` they are not
+// computed (3 of block 0's 4 last-round columns).  Per hash 281 lookups
+// instead of 320.
+template <int NG, bool PAIRED = false, typename Key>
+__device__ __forceinline__ void hash_pairs(const PermTE02 &T, const Key &K, const uint32_t (&x)[4], uint64_t tau,
+                                           uint32_t gid, bool all, uint32_t (&V)[NG][8]) {
+    uint32_t s[2 * NG][4];
+    __builtin_amdgcn_s_setprio(1);  // as in aes128_encrypt_n
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+        const uint64_t tw = (tau + static_cast<uint64_t>(j)) * 4u;
+        const uint32_t w[4] = {xor3(x[2], static_cast<uint32_t>(tw), K(0)),
+                               xor3(x[3], static_cast<uint32_t>(tw >> 32), K(1)), xor3(x[2], x[0], K(2)),
+                               xor3(x[3], x[1], K(3) ^ gid)};
+        uint32_t c[4];
+        const uint32_t c01 = T.first_round_pair(w, K, c);
+        __builtin_amdgcn_sched_barrier(0);
+        T.second_round_pair(c, c01, K, s[2 * j], s[2 * j + 1]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // Rounds 3..9 stay a loop, as in aes128_encrypt_n (PAIRED likewise).
+    auto round_to = [&](const uint32_t(&in)[2 * NG][4], uint32_t(&o)[2 * NG][4], int r) {
+#pragma unroll
+        for (int b = 0; b < 2 * NG; ++b) {
+            const uint32_t s0 = in[b][0], s1 = in[b][1], s2 = in[b][2], s3 = in[b][3];
+            o[b][0] = T.column(s0, s1, s2, s3, K, 4 * r);
+            o[b][1] = T.column(s1, s2, s3, s0, K, 4 * r + 1);
+            o[b][2] = T.column(s2, s3, s0, s1, K, 4 * r + 2);
+            o[b][3] = T.column(s3, s0, s1, s2, K, 4 * r + 3);
+        }
+    };
+    auto last_round = [&](const uint32_t(&in)[2 * NG][4]) {
+#pragma unroll
+        for (int j = 0; j < NG; ++j) {
+            const uint32_t a0 = in[2 * j][0], a1 = in[2 * j][1], a2 = in[2 * j][2], a3 = in[2 * j][3];
+            V[j][3] = T.last_column(a3, a0, a1, a2, K, 43);
+            V[j][0] = V[j][1] = V[j][2] = 0;
+            if (all) {
+                V[j][0] = T.last_column(a0, a1, a2, a3, K, 40);
+                V[j][1] = T.last_column(a1, a2, a3, a0, K, 41);
+                V[j][2] = T.last_column(a2, a3, a0, a1, K, 42);
+            }
+            const uint32_t b0 = in[2 * j + 1][0], b1 = in[2 * j + 1][1], b2 = in[2 * j + 1][2], b3 = in[2 * j + 1][3];
+            V[j][4] = T.last_column(b0, b1, b2, b3, K, 40);
+            V[j][5] = T.last_column(b1, b2, b3, b0, K, 41);
+            V[j][6] = T.last_column(b2, b3, b0, b1, K, 42);
+            V[j][7] = T.last_column(b3, b0, b1, b2, K, 43);
+        }
+    };
+    if constexpr (PAIRED) {
+        uint32_t t[2 * NG][4];
+#pragma unroll 1
+        for (int r = 3; r < 9; r += 2) {
+            round_to(s, t, r);
+            round_to(t, s, r + 1);
+        }
+        round_to(s, t, 9);
+        last_round(t);
+    } else {
+#pragma unroll 1
+        for (int r = 3; r < 10; ++r) round_to(s, s, r);
+        last_round(s);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    // Matyas-Meyer-Oseas feed-forward of the block input u ^ T.  The inputs
+    // are formed again from x and tau rather than kept through the rounds
+    // (opaque keeps the compiler from reusing the earlier values).
+    const uint32_t y0 = opaque(x[0]), y1 = opaque(x[1]), y2 = opaque(x[2]), y3 = opaque(x[3]);
+    const uint64_t tau2 = (static_cast<uint64_t>(opaque(static_cast<uint32_t>(tau >> 32))) << 32) |
+                          opaque(static_cast<uint32_t>(tau));
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+        const uint64_t tw = (tau2 + static_cast<uint64_t>(j)) * 4u;
+        const uint32_t lo = y2 ^ static_cast<uint32_t>(tw), hi = y3 ^ static_cast<uint32_t>(tw >> 32);
+        const uint32_t u2 = y2 ^ y0, u3 = xor3(y3, y1, gid);
+        V[j][3] ^= u3;
+        if (all) {
+            V[j][0] ^= lo;
+            V[j][1] ^= hi;
+            V[j][2] ^= u2;
+        }
+        V[j][4] ^= lo ^ 1u;
+        V[j][5] ^= hi;
+        V[j][6] ^= u2;
+        V[j][7] ^= u3;
+    }
+}
+
+// Limbs 0-2 of the fraction: the rest of block 0's output (the rare case).
+template <typename Key>
+__device__ __forceinline__ void first_limbs(const PermTE02 &T, const Key &K, const uint32_t (&x)[4], uint64_t tau,
+                                            uint32_t gid, uint32_t (&V)[8]) {
+    const uint64_t tw = tau * 4u;
+    const uint32_t in[4] = {x[2] ^ static_cast<uint32_t>(tw), x[3] ^ static_cast<uint32_t>(tw >> 32), x[2] ^ x[0],
+                            xor3(x[3], x[1], gid)};
+    uint32_t s[1][4] = {{in[0], in[1], in[2], in[3]}};
+    aes128_encrypt_n<1>(T, s, K);
+    static_for<3>([&](auto l) { V[l] = s[0][l] ^ in[l]; });
+}
+
+// The pad of a label over Z_m as one base-m number per packed word, right
+// aligned as the register labels: D[p] for p = kMaxW - W .. kMaxW - 1 holds
+// the word's digits, residue 0 the most significant.
+//
+// From limbs 3-7 alone (160 of the 256 bits): the pad is the first lambda
+// digits, 128 to 132 bits, and each multiplication by m^g moves that many
+// bits out at the top, so a word with r words after it needs only kPadLimbs[r]
+// limbs.  What is left out lowers the running fraction by less than the
+// final fraction's distance to ModConst::pad_amb: a digit can only be wrong
+// if the final fraction is at or above it (a missed carry leaves the fraction
+// just below 1 from that word on).  Returns that condition, which sends the
+// caller back for all limbs (pad_words_all); probability below 2^-14 per pad
+// (2^-18 for m = 37).  17 to 22 limb products per pad instead of 40 to 48.
+__device__ __forceinline__ bool pad_words_top(const uint32_t (&V)[8], const ModConst &mc, uint32_t (&D)[kMaxW]) {
+    uint32_t v[5] = {V[3], V[4], V[5], V[6], V[7]};
+    const int off = kMaxW - static_cast<int>(mc.W);
+    static_for<kMaxW>([&](auto p) {
+        D[p] = 0;
+        if (p >= off) {
+            constexpr int L = kPadLimbs[kMaxW - 1 - p];
+            const uint32_t pw = p == kMaxW - 1 ? mc.pw_last : mc.pw_g;
+            uint64_t carry = 0;
+            static_for<L>([&](auto l) {
+                const uint64_t t = static_cast<uint64_t>(v[5 - L + l]) * pw + carry;
+                v[5 - L + l] = static_cast<uint32_t>(t);
+                carry = t >> 32;
+            });
+            D[p] = static_cast<uint32_t>(carry);
+        }
+    });
+    return v[4] >= mc.pad_amb;
+}
+
+// The same from all eight limbs, any modulus (m = 2: each word is one limb).
+__device__ __forceinline__ void pad_words_all(uint32_t (&V)[8], const ModConst &mc, uint32_t (&D)[kMaxW]) {
+    static_for<kMaxW>([&](auto p) { D[p] = 0; });
+    if (mc.m == 2) {
+        static_for<4>([&](auto w) { D[w + 2] = bits_word(V, w); });
+        return;
+    }
+    const int off = kMaxW - static_cast<int>(mc.W);
+    static_for<kMaxW>([&](auto p) {
+        if (p >= off) D[p] = frac_carry_any(V, p == kMaxW - 1 ? mc.pw_last : mc.pw_g);
+    });
 }
 
 // Pad word w of the hash output over Z_m (words must be produced in order

@@ -189,6 +189,28 @@ void fill_mod_const(uint32_t m, ModConst *mc) {
     mc->fast = ok ? 1u : 0u;
     // fraction-multiplication digits: exact while (m^n)^2 < 2^32
     mc->fd = (static_cast<uint64_t>(part) * part < (1ull << 32)) ? 1u : 0u;
+    // Bound of the truncated pad (kPadLimbs): word w of W starts with limbs
+    // below the lowest kept one left out, less than 2^(-32 L) of the fraction,
+    // which the multiplications from word w to the last scale by m^(residues
+    // from word w on).  In units of 2^-32 of the final fraction, rounded up:
+    if (mc->fast) {
+        unsigned __int128 err = 1;
+        for (uint32_t w = 0; w < mc->W; ++w) {
+            const uint32_t L = kPadLimbs[mc->W - 1 - w], left = mc->lam - w * mc->g;
+            // ceil(m^left / 2^(32 (L - 1))), the power rounded up limb by limb
+            unsigned __int128 e = 1;
+            uint32_t shifted = 0;
+            for (uint32_t i = 0; i < left; ++i) {
+                e *= m;
+                if ((e >> 96) && shifted + 32 <= 32 * (L - 1)) {
+                    e = (e >> 32) + 1;
+                    shifted += 32;
+                }
+            }
+            err += (e >> (32 * (L - 1) - shifted)) + 1;
+        }
+        if (err < (1u << 18)) mc->pad_amb = 0xffffffffu - static_cast<uint32_t>(err);
+    }
     auto frac_mult = [](uint64_t M) { return M > 1 ? static_cast<uint32_t>((1ull << 32) / M + 1) : 0u; };
     for (int k = 0; k < 2; ++k) {
         const uint32_t nres = k ? mc->glast : mc->g;

@@ -70,7 +70,16 @@ struct ModConst {
     // b free bits above them.  sw_even masks the even fields, sw_ones has
     // bit 0 of each even field, sw_k holds 2^b - m in each even field.
     uint32_t sw_even, sw_ones, sw_k;
+    // Pad digits from the top 160 bits of the hash (kPadLimbs): they are right
+    // unless the top limb of the fraction left after the last word is at
+    // least pad_amb.  0: the pad always takes all 256 bits (m = 2, the moduli
+    // without the fast constants, or too few bits to spare).
+    uint32_t pad_amb;
 };
+
+// 32-bit limbs of the hash fraction that a packed word of the pad with r words
+// after it is taken from (of the five top limbs).
+constexpr int kPadLimbs[6] = {2, 3, 3, 4, 5, 5};
 
 // Gate descriptor packed in one word:
 //   bits 0-3 src modulus index, 4-7 dst modulus index, 8 kind (0 sub, 1 acc),

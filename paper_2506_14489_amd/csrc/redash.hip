@@ -149,21 +149,21 @@ __device__ __forceinline__ void fold_regs(const uint32_t (&T)[kMaxW], uint32_t (
 // Moduli without the fast constants (4 and 16, whose fields fill a word, and
 // the primes 41, 47, 53, 59 and 61, whose split parts are too large for the
 // 24-bit digit steps): one residue at a time with 32-bit divisions, over all
-// kMaxW positions in a rolled loop that rotates the label and the row by one
-// word per position (kMaxW rotations put both back in place).  The gadget
+// kMaxW positions in a rolled loop that rotates the label, the row and the pad
+// by one word per position (kMaxW rotations put label and row back in place).  The gadget
 // configurations in use all take the fast path.
-__device__ __forceinline__ void reg_update_generic(uint32_t e, const ModConst &mm, uint32_t (&V)[8],
+__device__ __forceinline__ void reg_update_generic(uint32_t e, const ModConst &mm, uint32_t (&Dw)[kMaxW],
                                                    uint32_t (&row)[kMaxW], uint32_t (&T)[kMaxW]) {
     const uint32_t coeff = eg_coeff(e), off = label_off(mm);
 #pragma unroll 1
     for (uint32_t p = 0; p < static_cast<uint32_t>(kMaxW); ++p) {
         const uint32_t l = next_word(T);
         const uint32_t rw = next_word(row);
+        uint32_t D = next_word(Dw);
         uint32_t res = l;
         if (p >= off) {
             const bool last = (p + 1 == static_cast<uint32_t>(kMaxW));
             const uint32_t nres = last ? mm.glast : mm.g;
-            uint32_t D = frac_carry_any(V, last ? mm.pw_last : mm.pw_g);
             res = 0;
             for (uint32_t j = nres; j-- > 0;) {
                 uint32_t pd;
@@ -190,26 +190,25 @@ __device__ __forceinline__ void reg_update_generic(uint32_t e, const ModConst &m
 // (residues per word, bits per residue) known at compile time: the shape is
 // dispatched once per gate, not once per word.
 template <bool ACC, bool TAB, int NR, int BB>
-__device__ __forceinline__ void reg_full_words(const ModConst &mm, uint32_t coeff, uint32_t (&V)[8],
+__device__ __forceinline__ void reg_full_words(const ModConst &mm, uint32_t coeff, const uint32_t (&D)[kMaxW],
                                                const uint32_t (&row)[kMaxW], uint32_t (&T)[kMaxW], uint32_t tk) {
     const uint32_t off = label_off(mm);
     static_for<kMaxW - 1>([&](auto p) {
         if (p >= static_cast<int>(off)) {
-            const uint32_t D = frac_mul_carry(V, mm.pw_g);
-            T[p] = fast_word_c<ACC, NR, BB, TAB>(D, mm.lo_M_f, mm.lo_s_f, mm.pw_lo_f, mm.fc_hi_f, mm.fc_lo_f, row[p],
+            T[p] = fast_word_c<ACC, NR, BB, TAB>(D[p], mm.lo_M_f, mm.lo_s_f, mm.pw_lo_f, mm.fc_hi_f, mm.fc_lo_f, row[p],
                                                  T[p], coeff, mm, tk);
         }
     });
 }
 
 template <bool ACC, bool TAB>
-__device__ __forceinline__ void reg_update_fast(uint32_t e, const ModConst &mm, uint32_t (&V)[8],
+__device__ __forceinline__ void reg_update_fast(uint32_t e, const ModConst &mm, const uint32_t (&D)[kMaxW],
                                                 const uint32_t (&row)[kMaxW], uint32_t (&T)[kMaxW], uint32_t tk) {
     const uint32_t coeff = eg_coeff(e);
     // full words: g = floor(32 / b) residues of b bits
     switch (mm.fd ? mm.g | (mm.b << 8) : 0u) {
 #define REDASH_FULL(NR, BB) \
-    case (NR) | ((BB) << 8): reg_full_words<ACC, TAB, NR, BB>(mm, coeff, V, row, T, tk); break;
+    case (NR) | ((BB) << 8): reg_full_words<ACC, TAB, NR, BB>(mm, coeff, D, row, T, tk); break;
         REDASH_FULL(16, 2) REDASH_FULL(10, 3) REDASH_FULL(8, 4) REDASH_FULL(6, 5) REDASH_FULL(5, 6)
         REDASH_FULL(4, 7) REDASH_FULL(4, 8)
 #undef REDASH_FULL
@@ -217,15 +216,13 @@ __device__ __forceinline__ void reg_update_fast(uint32_t e, const ModConst &mm, 
             const uint32_t off = label_off(mm);
             static_for<kMaxW - 1>([&](auto p) {
                 if (p >= static_cast<int>(off)) {
-                    const uint32_t D = frac_mul_carry(V, mm.pw_g);
-                    T[p] = fast_word<ACC>(D, mm.g, mm.nlo_f, mm.lo_M_f, mm.lo_s_f, mm.pw_lo_f, row[p], T[p], coeff,
+                    T[p] = fast_word<ACC>(D[p], mm.g, mm.nlo_f, mm.lo_M_f, mm.lo_s_f, mm.pw_lo_f, row[p], T[p], coeff,
                                           mm);
                 }
             });
         }
     }
-    const uint32_t D = frac_mul_carry(V, mm.pw_last);
-    T[kMaxW - 1] = fast_word_any<ACC, TAB>(D, mm.glast, mm.nlo_l, mm.lo_M_l, mm.lo_s_l, mm.pw_lo_l, mm.fc_hi_l,
+    T[kMaxW - 1] = fast_word_any<ACC, TAB>(D[kMaxW - 1], mm.glast, mm.nlo_l, mm.lo_M_l, mm.lo_s_l, mm.pw_lo_l, mm.fc_hi_l,
                                            mm.fc_lo_l, row[kMaxW - 1], T[kMaxW - 1], coeff, mm, tk);
 }
 
@@ -235,28 +232,29 @@ __device__ __forceinline__ void reg_update_fast(uint32_t e, const ModConst &mm, 
 // scaling modulus).  For an output modulus m <= 42 the product c (v mod m)
 // mod m comes from the gate's byte table in LDS: a sub gate's new residue is
 // T[l + 2m - p - r], an acc gate's is l + T[p + r] reduced once.
-__device__ __forceinline__ void reg_update(uint32_t g, uint32_t e, const ModConst &mm, uint32_t (&V)[8],
+// D: the gate's pad (pad_words_top, pad_words_all).
+__device__ __forceinline__ void reg_update(uint32_t g, uint32_t e, const ModConst &mm, uint32_t (&D)[kMaxW],
                                            uint32_t (&row)[kMaxW], uint32_t (&T)[kMaxW]) {
     if (mm.m == 2) {  // W = 4: positions 2..5
         const bool flip = eg_kind(e) == 0 || (eg_coeff(e) & 1u);  // sub: q^{-1} = 1 mod 2
         if (flip) {
-            static_for<4>([&](auto w) { T[w + 2] ^= bits_word(V, w) ^ row[w + 2]; });
+            static_for<4>([&](auto w) { T[w + 2] ^= D[w + 2] ^ row[w + 2]; });
         }
     } else if (eg_tab(e)) {
         const uint32_t tk = kEvalTableBase + g * kTableBytes + (eg_kind(e) ? 0u : mm.two_m);
         if (eg_kind(e)) {
-            reg_update_fast<true, true>(e, mm, V, row, T, tk);
+            reg_update_fast<true, true>(e, mm, D, row, T, tk);
         } else {
-            reg_update_fast<false, true>(e, mm, V, row, T, tk);
+            reg_update_fast<false, true>(e, mm, D, row, T, tk);
         }
     } else if (mm.fast) {
         if (eg_kind(e)) {
-            reg_update_fast<true, false>(e, mm, V, row, T, 0);
+            reg_update_fast<true, false>(e, mm, D, row, T, 0);
         } else {
-            reg_update_fast<false, false>(e, mm, V, row, T, 0);
+            reg_update_fast<false, false>(e, mm, D, row, T, 0);
         }
     } else {
-        reg_update_generic(e, mm, V, row, T);
+        reg_update_generic(e, mm, D, row, T);
     }
 }
 
@@ -277,6 +275,29 @@ __device__ __forceinline__ void stage_free_op_tables_e(const EvalPlan &P, uint32
     }
 }
 
+// Gate g's pad from its hash fraction V: from the leading limbs (V[0..2] need
+// not be there), or from all of them when the modulus takes all.  Where some
+// lane's digits could depend on limbs 0-2 (about once in 2^12 waves) the
+// wave hashes the gate's first block again for them: digit(x) reads and folds
+// the digit label, tau() is the tweak.
+template <typename Digit, typename Tau>
+__device__ __forceinline__ void gate_pad(const PermTE02 &TT, const uint32_t *K, uint32_t gid, const ModConst &mm,
+                                         uint32_t (&V)[8], uint32_t (&D)[kMaxW], Digit &&digit, Tau &&tau) {
+    if (mm.pad_amb != 0) {
+        const uint32_t v3 = V[3], v4 = V[4], v5 = V[5], v6 = V[6], v7 = V[7];
+        if (__builtin_expect(!__any(pad_words_top(V, mm, D)), 1)) return;
+        uint32_t x[4];
+        digit(x);
+        first_limbs(TT, LdsKey{K}, x, tau(), gid, V);
+        V[3] = v3;
+        V[4] = v4;
+        V[5] = v5;
+        V[6] = v6;
+        V[7] = v7;
+    }
+    pad_words_all(V, mm, D);
+}
+
 // One step's NG gates g, g+1 (NG = 2) or g: requests their rows (the colour
 // is known before hashing), then runs the 2 NG AES blocks interleaved.
 //
@@ -286,6 +307,11 @@ __device__ __forceinline__ void stage_free_op_tables_e(const EvalPlan &P, uint32
 // across the whole gadget.
 __device__ __forceinline__ uint64_t mad64(uint32_t x, uint32_t y, uint64_t z) {
     return static_cast<uint64_t>(x) * y + z;
+}
+
+// Gate g's tweak for local gadget a.
+__device__ __forceinline__ uint64_t gate_tweak(const EvalPlan &P, uint32_t a, uint32_t g) {
+    return mad64(opaque(a), P.G, P.a0 * P.G + g);
 }
 
 template <int NG>
@@ -306,10 +332,14 @@ __device__ __forceinline__ void step_hash(const EvalPlan &P, uint32_t g, uint32_
             });
         }
     });
+    bool all = false;
+    static_for<NG>([&](auto j) { all = all || P.mod[eg_dst(P.egate[g + j])].pad_amb == 0; });
     uint32_t Vn[NG][8];
-    const uint64_t tau = mad64(opaque(a), P.G, P.a0 * P.G + g);
-    hash_fraction_n<NG>(TT, LdsKey{K}, x[0], x[1], x[2], x[3], tau, P.gid, Vn);
-    static_for<NG>([&](auto j) { static_for<8>([&](auto l) { V[j][l] = Vn[j][l]; }); });
+    hash_pairs<NG>(TT, LdsKey{K}, x, gate_tweak(P, a, g), P.gid, all, Vn);
+    // (a single gate clears the second's, which would otherwise be carried
+    // from step to step in registers)
+    static_for<2>([&](auto j) { static_for<8>([&](auto l) { V[j][l] = j < NG ? Vn[j < NG ? j : 0][l] : 0u; }); });
+    if constexpr (NG == 1) static_for<kMaxW>([&](auto w) { row[1][w] = 0; });
 }
 
 template <int BLOCK>
@@ -346,22 +376,28 @@ k_eval(const EvalPlan P, const uint32_t *__restrict__ in, const uint32_t *__rest
             // and decode flags it.
             const ModConst mq = P.mod[st_dmod(sd)];
             const uint32_t q = mq.m;
-            uint32_t x[4] = {0, 0, 0, 0}, w0;
-            if (st_dloc(sd) == kDigSlot0) {  // the block's first target, now in T[1]
-                switch (label_off(mq)) {
-                    case 0: fold_regs<0>(T[1], x); w0 = T[1][0]; break;
-                    case 1: fold_regs<1>(T[1], x); w0 = T[1][1]; break;
-                    default: fold_regs<2>(T[1], x); w0 = T[1][2]; break;
+            auto digit = [&](uint32_t(&x)[4]) -> uint32_t {
+                static_for<4>([&](auto l) { x[l] = 0; });
+                uint32_t w0;
+                if (st_dloc(sd) == kDigSlot0) {  // the block's first target, now in T[1]
+                    switch (label_off(mq)) {
+                        case 0: fold_regs<0>(T[1], x); w0 = T[1][0]; break;
+                        case 1: fold_regs<1>(T[1], x); w0 = T[1][1]; break;
+                        default: fold_regs<2>(T[1], x); w0 = T[1][2]; break;
+                    }
+                } else {
+                    const uint32_t *dig = LB.base(st_dloc(sd), mq);
+                    w0 = LB.get(dig, 0);
+                    x[0] = w0;
+                    static_for<kMaxW - 1>([&](auto w1) {
+                        constexpr int w = decltype(w1)::value + 1;
+                        if (w < static_cast<int>(mq.W)) x[w & 3] ^= LB.get(dig, w);
+                    });
                 }
-            } else {
-                const uint32_t *dig = LB.base(st_dloc(sd), mq);
-                w0 = LB.get(dig, 0);
-                x[0] = w0;
-                static_for<kMaxW - 1>([&](auto w1) {
-                    constexpr int w = decltype(w1)::value + 1;
-                    if (w < static_cast<int>(mq.W)) x[w & 3] ^= LB.get(dig, w);
-                });
-            }
+                return w0;
+            };
+            uint32_t x[4];
+            const uint32_t w0 = digit(x);
             uint32_t colour = w0 & mq.mask;
             if (colour >= q) colour = 0;
             const uint32_t g = st_gate(sd);
@@ -378,7 +414,9 @@ k_eval(const EvalPlan P, const uint32_t *__restrict__ in, const uint32_t *__rest
             for (uint32_t j = 0; j < ng; ++j) {
                 const uint32_t e = P.egate[g + j];
                 const ModConst mm = P.mod[eg_dst(e)];
-                reg_update(g + j, e, mm, V[0], row[0], T[0]);
+                uint32_t D[kMaxW];
+                gate_pad(TT, K, P.gid, mm, V[0], D, digit, [&] { return gate_tweak(P, a, g + j); });
+                reg_update(g + j, e, mm, D, row[0], T[0]);
                 if (two) {
                     swap_slots(T);
                     static_for<8>([&](auto l) { V[0][l] = V[1][l]; });
@@ -482,10 +520,13 @@ k_eval_split(const Plan P, const uint32_t *__restrict__ in, const uint32_t *__re
                 }
                 uint32_t T[kMaxW];
                 load_label(T, LB, gate_tsrc(d), mm, gate_tsrc(d) != kLocZero);
-                uint32_t Vn[1][8];
-                hash_fraction_n<1, true>(TT, LdsKey{K}, x[0], x[1], x[2], x[3], tau0 + g + i, P.gid, Vn);
+                uint32_t Vn[1][8], D[kMaxW];
+                hash_pairs<1, true>(TT, LdsKey{K}, x, tau0 + g + i, P.gid, mm.pad_amb == 0, Vn);
+                gate_pad(TT, K, P.gid, mm, Vn[0], D,
+                         [&](uint32_t(&f)[4]) { static_for<4>([&](auto l) { f[l] = x[l]; }); },
+                         [&] { return tau0 + g + i; });
                 const uint32_t e = gate_dst(d) | (gate_kind(d) << 4) | (gate_tab(d) << 5) | (gate_coeff(d) << 6);
-                reg_update(g + i, e, mm, Vn[0], row, T);
+                reg_update(g + i, e, mm, D, row, T);
                 store_label(T, LB, gate_tdst(d), mm);
             }
             toff += P.n * (q - 1) * P.mod[gate_dst(d)].W;

@@ -54,6 +54,87 @@ static uint64_t ipow(uint64_t m, uint32_t e) {
     return r;
 }
 
+// The words of a pad (base-m numbers, most significant word first) from the
+// fraction's limbs: all eight, or the five top ones through kPadLimbs as the
+// kernels take them; the return value is the top limb left at the end.
+static uint32_t pad_all(const ModConst &mc, const uint32_t (&V)[8], uint32_t (&D)[6]) {
+    uint32_t v[8];
+    memcpy(v, V, sizeof v);
+    for (uint32_t w = 0; w < mc.W; ++w) {
+        uint64_t carry = 0;
+        for (int l = 0; l < 8; ++l) {
+            const uint64_t t = static_cast<uint64_t>(v[l]) * (w + 1 == mc.W ? mc.pw_last : mc.pw_g) + carry;
+            v[l] = static_cast<uint32_t>(t);
+            carry = t >> 32;
+        }
+        D[w] = static_cast<uint32_t>(carry);
+    }
+    return v[7];
+}
+
+static uint32_t pad_top(const ModConst &mc, const uint32_t (&V)[8], uint32_t (&D)[6]) {
+    uint32_t v[5];
+    memcpy(v, V + 3, sizeof v);
+    for (uint32_t w = 0; w < mc.W; ++w) {
+        uint64_t carry = 0;
+        for (int l = 5 - kPadLimbs[mc.W - 1 - w]; l < 5; ++l) {
+            const uint64_t t = static_cast<uint64_t>(v[l]) * (w + 1 == mc.W ? mc.pw_last : mc.pw_g) + carry;
+            v[l] = static_cast<uint32_t>(t);
+            carry = t >> 32;
+        }
+        D[w] = static_cast<uint32_t>(carry);
+    }
+    return v[4];
+}
+
+// Pads from the leading limbs against pads from all of them: where the top
+// limb left is below pad_amb they are equal.  Fractions: random ones, and
+// ones a few units of a low limb around a number with j digits (whose later
+// digits are all 0 or all m - 1, where a left-out carry matters).
+static void check_pad(const ModConst &mc) {
+    static long wrong = 0;  // pads that the check sends back and that were indeed wrong
+    uint64_t rng = 88172645463325252ull + mc.m;
+    auto next = [&] {
+        rng ^= rng << 13;
+        rng ^= rng >> 7;
+        rng ^= rng << 17;
+        return rng;
+    };
+    for (int it = 0; it < 4000; ++it) {
+        uint32_t V[8] = {};
+        if (it % 4 == 0) {
+            for (auto &l : V) l = static_cast<uint32_t>(next() >> 16);
+        } else {
+            // sum of digits d_i m^-i, i = 1 .. j, rounded down
+            const uint32_t j = 1 + static_cast<uint32_t>(next() % mc.lam);
+            for (uint32_t i = 0; i < j; ++i) {
+                uint64_t r = next() % mc.m;
+                for (int l = 7; l >= 0; --l) {
+                    const uint64_t t = (r << 32) | V[l];
+                    V[l] = static_cast<uint32_t>(t / mc.m);
+                    r = t % mc.m;
+                }
+            }
+            // a step up or down in limb 0 .. 4
+            const int at = static_cast<int>(next() % 5);
+            const int64_t by = static_cast<int64_t>(next() % 64) - 32;
+            int64_t c = by;
+            for (int l = at; l < 8 && c; ++l) {
+                const int64_t t = static_cast<int64_t>(V[l]) + c;
+                V[l] = static_cast<uint32_t>(t);
+                c = t >> 32;
+            }
+        }
+        uint32_t A[6], B[6];
+        pad_all(mc, V, A);
+        const uint32_t left = pad_top(mc, V, B);
+        const bool same = memcmp(A, B, mc.W * sizeof(uint32_t)) == 0;
+        CHECK(same || left >= mc.pad_amb, "m=%u pad from the leading limbs", mc.m);
+        wrong += !same;
+    }
+    if (mc.m == 37) CHECK(wrong > 0, "the check is never needed");
+}
+
 static void check_modulus(uint32_t m) {
     ModConst mc;
     fill_mod_const(m, &mc);
@@ -110,8 +191,10 @@ static void check_modulus(uint32_t m) {
             CHECK(inv < m && (a * inv) % m == 1, "m=%u inverse of %u", m, a);
         }
     }
+    CHECK(mc.fast ? mc.pad_amb > 0xffffffffu - (1u << 18) : mc.pad_amb == 0, "m=%u pad_amb", m);
     if (!mc.fast) return;
     CHECK(m > 2, "m=%u fast", m);
+    check_pad(mc);
     // one reduction per residue: floor(x/m) = umulhi(x, ceil(2^32/m)) for x < 3 m^2
     for (uint32_t x = 0; x < 3 * m * m; ++x) CHECK(umulhi(x, mc.red_M) == x / m, "m=%u red x=%u", m, x);
     CHECK(mc.two_m == 2 * m, "m=%u two_m", m);
