@@ -54,6 +54,11 @@ __device__ __forceinline__ uint32_t opaque(uint32_t v) {
     return v;
 }
 
+__device__ __forceinline__ uint64_t opaque64(uint64_t v) {
+    asm("" : "+v"(v));
+    return v;
+}
+
 // A wave-uniform value masked to 24 bits in the calling block.  Instruction
 // selection only uses v_mul_u32_u24 when it sees both operands' 24-bit bound
 // in the same basic block; a mask hoisted out of the block (as the compiler
@@ -434,31 +439,28 @@ __device__ __forceinline__ uint32_t div_const(uint32_t x, uint32_t M, uint32_t s
     return fix ? (t + ((x - t) >> 1)) >> s : t >> s;
 }
 
-// Evaluator fast path for one packed word over Z_m (m > 2, mc.fast set).
-// D holds the word's nres pad digits as a base-m number (residue 0 the most
-// significant digit).  For each residue j, with pad digit p, row residue r
-// and label residue l:
-//   sub gate (ACC = false): l <- c (l - p - r)      computed as c (l + 2m - p - r) < 3 m^2
-//   acc gate (ACC = true):  l <- l + c (p + r)      computed unreduced, < 2 m^2
-// followed by one multiply-shift reduction.  D is first split as
-// hi * m^nlo + lo so that every further digit division works on < 2^24.
-template <bool ACC>
+// Evaluator fast path for one packed word over Z_m (m > 2, mc.fast set), any
+// shape.  D holds the word's nres pad digits as a base-m number (residue 0 the
+// most significant digit).  The result holds c' (p + s) mod m for every
+// residue, p its pad digit, r the row's and l the label's residue:
+//   sub gate, l <- c (l - p - r):  c' = m - c, s = r - l + m, the new residue
+//   acc gate, l <- l + c (p + r):  c' = c, s = r, the summand
+// (p + s < 3m, c' (p + s) < 3 m^2: one multiply-shift reduction).  D is first
+// split as hi * m^nlo + lo so that every further digit division works on
+// < 2^24.
 __device__ __forceinline__ uint32_t fast_word(uint32_t D, uint32_t nres, uint32_t nlo, uint32_t lo_M, uint32_t lo_s,
-                                              uint32_t pw_lo, uint32_t rw, uint32_t l, uint32_t c,
+                                              uint32_t pw_lo, uint32_t rw, uint32_t l, bool acc, uint32_t cc,
                                               const ModConst &mc) {
-    const uint32_t m = mc.m, b = mc.b, mask = mc.mask;
+    const uint32_t m = mc.m, b = mc.b, mask = mc.mask, ms = acc ? 0u : m, ml = acc ? 0u : mask;
     uint32_t hi = D, lo = 0;
     if (nlo) {
         hi = __umulhi(D, lo_M) >> lo_s;
         lo = D - mul24(hi, pw_lo);
     }
-    // mc.two_m (= 2m) is a separate field on purpose: were the compiler to
-    // see it as 2 * m, it would fold "+ 2m - (x - q m)" into (q + 2) m, a
-    // product it cannot prove to be 24-bit (quarter-rate multiply).
     auto residue = [&](uint32_t p, uint32_t j) -> uint32_t {
         const uint32_t r = (rw >> (b * j)) & mask;
-        const uint32_t lj = (l >> (b * j)) & mask;
-        const uint32_t v = ACC ? lj + mul24(c, p + r) : mul24(c, lj + mc.two_m - p - r);
+        const uint32_t lj = (l >> (b * j)) & ml;
+        const uint32_t v = mul24(cc, (p + r + ms - lj) & 0xffffu);
         const uint32_t q = __umulhi(v, mc.red_M);
         return (v - mul24(q, m)) << (b * j);
     };
@@ -484,92 +486,110 @@ __device__ __forceinline__ uint32_t fast_word(uint32_t D, uint32_t nres, uint32_
 }
 
 // The ND base-m digits of x < m^ND (with (m^ND)^2 < 2^32), most significant
-// first, handed to f(digit, integral_constant<J0 + k>) for k = 0..ND-1:
+// first, handed to f(digit + add, integral_constant<J0 + k>) for k = 0..ND-1:
 // F = x C mod 2^32 with C = floor(2^32 / m^ND) + 1 approximates the fraction
-// x / m^ND from above by less than 2^-32 x, so each umulhi(F, m) is the next
-// digit exactly, and F m mod 2^32 the remaining fraction.
+// x / m^ND from above by less than 2^-32 x, so the high half of each product
+// F m is the next digit exactly, and the low half the remaining fraction: one
+// 32 x 32 + 64-bit multiply-add per digit, which also adds `add` to it (given
+// as add 2^32; opaque64 keeps the compiler from adding it separately).
 template <int ND, int J0, typename Fn>
-__device__ __forceinline__ void frac_digits(uint32_t x, uint32_t C, uint32_t m, Fn &&f) {
-    if constexpr (ND > 0) {
+__device__ __forceinline__ void frac_digits(uint32_t x, uint32_t C, uint32_t m, uint64_t add, Fn &&f) {
+    if constexpr (ND == 1) {
+        f(x + static_cast<uint32_t>(add >> 32), std::integral_constant<int, J0>{});
+    } else if constexpr (ND > 1) {
         uint32_t F = x * C;
         static_for<ND>([&](auto k) {
-            constexpr int kk = decltype(k)::value;
-            f(__umulhi(F, m), std::integral_constant<int, J0 + kk>{});
-            if constexpr (kk + 1 < ND) F *= m;
+            const uint64_t t = static_cast<uint64_t>(F) * m + add;
+            f(static_cast<uint32_t>(t >> 32), std::integral_constant<int, J0 + decltype(k)::value>{});
+            F = static_cast<uint32_t>(t);
         });
     }
 }
 
-// fast_word with the residue count and field width known at compile time:
-// every loop unrolled, every shift an immediate.
+// The mask of the even fields of a word of NRES fields of B bits, and of its
+// odd fields shifted down by B.
+template <int NRES, int B>
+constexpr uint32_t even_fields(int first) {
+    uint32_t v = 0;
+    for (int j = first; j < NRES; j += 2) v |= ((1u << B) - 1u) << (B * (j - first));
+    return v;
+}
+
+// One packed word of a gate's free operation with the residue count and field
+// width known at compile time: c' (p + s) mod m for every residue, p the pad
+// digit, s = r - l + m (c' = -c: a sub gate's new residue) or s = r (c' = c: an
+// acc gate's summand), r the row's and l the label's residue.
 //
-// With TAB, the product c (v mod m) mod m comes from the gate's byte table in
-// LDS (v < 3m, see free_op_table): tk is the table's LDS address, plus 2m for
-// a sub gate, so the sub gate's byte address is lj + tk - p - r.
-//
-// The digits of each part come from fraction multiplication (ModConst::fd):
-// two full-rate multiplies per digit instead of a division step.
-template <bool ACC, int NRES, int B, bool TAB>
+// s is formed for the whole word at once, the even and the odd fields apart so
+// that each has room for 2m - 1: km holds m in every even field and lmask all
+// ones for a sub gate, both 0 for an acc gate (in vector registers: the
+// one-pass adds and masks take two cycles a wave with vector operands, four
+// with a scalar one).  Per residue there remain one multiply-add (the digit,
+// frac_digits), one field extraction, one add, the product and one insert.
+// With TAB the product comes from the gate's byte table in LDS (entry y is
+// c' y mod m, y < 3m): tk is the table's LDS address times 2^32, added to the
+// digit.
+template <int NRES, int B, bool TAB>
 __device__ __forceinline__ uint32_t fast_word_c(uint32_t D, uint32_t lo_M, uint32_t lo_s, uint32_t pw_lo,
-                                                uint32_t c_hi, uint32_t c_lo, uint32_t rw, uint32_t l, uint32_t c,
-                                                const ModConst &mc, uint32_t tk) {
+                                                uint32_t c_hi, uint32_t c_lo, uint32_t rw, uint32_t l, uint32_t lmask,
+                                                uint32_t km, uint32_t cc, const ModConst &mc, uint64_t tk) {
     constexpr int NLO = NRES / 2, NHI = NRES - NLO;
-    constexpr uint32_t MASK = (1u << B) - 1u;
-    const uint32_t m = uniform24(mc.m);
-    c = uniform24(c);
+    constexpr uint32_t E = even_fields<NRES, B>(0), O = even_fields<NRES, B>(1);
+    const uint32_t lx = opaque(l & lmask);
+    const uint32_t se = (rw & E) + km - (lx & E);
+    uint32_t so = 0;
+    if constexpr (NRES > 1) so = ((rw >> B) & O) + km - ((lx >> B) & O);
     uint32_t hi = D, lo = 0;
     if constexpr (NLO > 0) {
         hi = __umulhi(D, lo_M) >> lo_s;
         lo = D - mul24(hi, pw_lo);
     }
-    uint32_t res = 0;
-    // Every multiply below must see both operands' 24-bit bound in this block
-    // (v_mul_u32_u24): shifted quotients and the sub gate's difference go
-    // through a bit-field extract of width 24 or 16, whose bound the
-    // instruction selector always sees (one op, like the shift it replaces).
+    uint32_t t[NRES];
     auto residue = [&](uint32_t p, auto jc) {
-        constexpr int j = decltype(jc)::value;
-        const uint32_t r = (rw >> (B * j)) & MASK;
-        const uint32_t lj = (l >> (B * j)) & MASK;
+        constexpr int j = decltype(jc)::value, at = B * (j - j % 2);
+        uint32_t y = j % 2 ? so : se;
+        y = y >> at;
+        // (km fills every even field of a full word: the fields above the
+        // last residue are dropped here and below)
+        if constexpr (at + 2 * B < 32) y &= (1u << (2 * B)) - 1u;
+        y += p;
         if constexpr (TAB) {
-            if constexpr (ACC) {
-                const uint32_t x = lj + lds_read_u8(tk + p + r);  // < 2m
-                res |= umin(x, x - m) << (B * j);
-            } else {
-                res |= lds_read_u8(lj + tk - p - r) << (B * j);
-            }
+            t[j] = lds_read_u8(y);
         } else {
-            const uint32_t v = ACC ? lj + mul24(c, __builtin_amdgcn_ubfe(p + r, 0, 16))
-                                   : mul24(c, __builtin_amdgcn_ubfe(lj + mc.two_m - p - r, 0, 16));
+            // every multiply must see both operands' 24-bit bound in this block
+            const uint32_t v = mul24(uniform24(cc), __builtin_amdgcn_ubfe(y, 0, 16));
             const uint32_t q = __umulhi(v, mc.red_M);
             // (opaque: a shift folded into the product would widen its operand)
-            res |= opaque(v - mul24(q, m)) << (B * j);
+            t[j] = opaque(v - mul24(q, uniform24(mc.m)));
         }
     };
     // high part: residues 0..NHI-1; low part: NHI..NRES-1 (most significant first)
-    frac_digits<NHI, 0>(hi, c_hi, mc.m, residue);
-    frac_digits<NLO, NHI>(lo, c_lo, mc.m, residue);
+    frac_digits<NHI, 0>(hi, c_hi, mc.m, TAB ? tk : 0u, residue);
+    frac_digits<NLO, NHI>(lo, c_lo, mc.m, TAB ? tk : 0u, residue);
+    // (opaque: one shift-or per residue; a shift and half a three-way or
+    // otherwise, which take half as long again)
+    uint32_t res = t[0];
+    static_for<NRES - 1>([&](auto j) { res = opaque(res | (t[j + 1] << (B * (j + 1)))); });
     return res;
 }
 
 // Dispatch on (residues in the word, bits per residue): the combinations
 // of the primes up to 37 and of the short bases' moduli (8, 32, 97, 107,
 // 128, 167, 173) are unrolled, anything else takes the loops.
-template <bool ACC, bool TAB>
+template <bool TAB>
 __device__ __forceinline__ uint32_t fast_word_any(uint32_t D, uint32_t nres, uint32_t nlo, uint32_t lo_M,
                                                   uint32_t lo_s, uint32_t pw_lo, uint32_t c_hi, uint32_t c_lo,
-                                                  uint32_t rw, uint32_t l, uint32_t c, const ModConst &mc,
-                                                  uint32_t tk) {
-    if (!mc.fd) return fast_word<ACC>(D, nres, nlo, lo_M, lo_s, pw_lo, rw, l, c, mc);
-    switch (nres | (mc.b << 8)) {
+                                                  uint32_t rw, uint32_t l, uint32_t lmask, uint32_t km, bool acc,
+                                                  uint32_t cc, const ModConst &mc, uint64_t tk) {
+    switch (mc.fd ? nres | (mc.b << 8) : 0u) {
 #define REDASH_FW(NR, BB)        \
     case (NR) | ((BB) << 8): \
-        return fast_word_c<ACC, NR, BB, TAB>(D, lo_M, lo_s, pw_lo, c_hi, c_lo, rw, l, c, mc, tk);
+        return fast_word_c<NR, BB, TAB>(D, lo_M, lo_s, pw_lo, c_hi, c_lo, rw, l, lmask, km, cc, mc, tk);
         REDASH_FW(16, 2) REDASH_FW(1, 2) REDASH_FW(10, 3) REDASH_FW(6, 3) REDASH_FW(8, 4) REDASH_FW(6, 4)
         REDASH_FW(3, 4) REDASH_FW(6, 5) REDASH_FW(5, 5) REDASH_FW(3, 5) REDASH_FW(2, 5) REDASH_FW(1, 5)
         REDASH_FW(5, 6) REDASH_FW(3, 3) REDASH_FW(4, 7) REDASH_FW(3, 7) REDASH_FW(4, 8) REDASH_FW(2, 8)
 #undef REDASH_FW
-        default: return fast_word<ACC>(D, nres, nlo, lo_M, lo_s, pw_lo, rw, l, c, mc);
+        default: return fast_word(D, nres, nlo, lo_M, lo_s, pw_lo, rw, l, acc, cc, mc);
     }
 }
 
@@ -594,8 +614,8 @@ __device__ __forceinline__ uint32_t row_word_c(uint32_t D, uint32_t lo_M, uint32
         const uint32_t d = ((bw >> (B * j)) & MASK) - p;
         res |= umin(d, d + m) << (B * j);
     };
-    frac_digits<NHI, 0>(hi, c_hi, mc.m, residue);
-    frac_digits<NLO, NHI>(lo, c_lo, mc.m, residue);
+    frac_digits<NHI, 0>(hi, c_hi, mc.m, 0u, residue);
+    frac_digits<NLO, NHI>(lo, c_lo, mc.m, 0u, residue);
     return res;
 }
 
@@ -861,7 +881,7 @@ __device__ __forceinline__ bool pad_words_top(const uint32_t (&V)[8], const ModC
     const int off = kMaxW - static_cast<int>(mc.W);
     static_for<kMaxW>([&](auto p) {
         D[p] = 0;
-        if (p >= off) {
+        if (p > 0 || off == 0) {  // five or six words where pad_amb is set
             constexpr int L = kPadLimbs[kMaxW - 1 - p];
             const uint32_t pw = p == kMaxW - 1 ? mc.pw_last : mc.pw_g;
             uint64_t carry = 0;

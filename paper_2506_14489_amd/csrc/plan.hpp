@@ -100,7 +100,8 @@ constexpr uint32_t gate_coeff(uint32_t d) { return (d >> 16) & 255u; }
 
 // Free-operation tables: gate g < ntab whose output modulus m satisfies
 // 2 < m <= kTableMaxModulus (and has the fast constants) gets 128 bytes of
-// LDS holding c (v mod m) mod m for v < 3m, c the gate's coefficient.  The
+// LDS holding c' y mod m for y < 3m, c' the gate's coefficient, negated for a
+// sub gate (fast_word).  The
 // evaluator then needs no multiply and no reduction per residue.  A table of
 // at most 128 bytes spans the 32 LDS banks once: lookups never conflict.
 constexpr uint32_t kTableBytes = 128;

@@ -77,21 +77,25 @@ struct LabelBufs {
     }
 };
 
-// Fills the free-operation tables (gates 0..ntab-1 that have one): byte v of
-// gate g's table is c (v mod m) mod m.  Wave w fills gates w, w + waves, ...
+// A gate's free-operation table, four entries a lane: entry y is c' y mod m
+// with c' = -c for a sub gate and c for an acc gate (fast_word).
+__device__ __forceinline__ uint32_t free_op_entries(uint32_t lane, uint32_t kind, uint32_t c, uint32_t m) {
+    const uint32_t cc = kind ? c : m - c;
+    uint32_t w = 0;
+    for (uint32_t k = 0; k < 4; ++k) w |= ((cc * (4 * lane + k)) % m) << (8 * k);
+    return w;
+}
+
+// Fills the free-operation tables (gates 0..ntab-1 that have one).  Wave w
+// fills gates w, w + waves, ...
 __device__ __forceinline__ void stage_free_op_tables(const Plan &P, uint32_t *lds, int tid, uint32_t nwaves) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(tid) / 64u);
     const uint32_t lane = static_cast<uint32_t>(tid) % 64u;
     for (uint32_t g = wave; g < P.ntab; g += nwaves) {
         const uint32_t d = P.gate[g];
         if (!gate_tab(d) || lane >= kTableBytes / 4) continue;
-        const uint32_t m = P.mod[gate_dst(d)].m, c = gate_coeff(d);
-        uint32_t w = 0;
-        for (uint32_t k = 0; k < 4; ++k) {
-            const uint32_t v = 4 * lane + k;
-            w |= ((c * (v % m)) % m) << (8 * k);
-        }
-        lds[(kEvalTableBase + g * kTableBytes) / 4 + lane] = w;
+        lds[(kEvalTableBase + g * kTableBytes) / 4 + lane] =
+            free_op_entries(lane, gate_kind(d), gate_coeff(d), P.mod[gate_dst(d)].m);
     }
 }
 
@@ -188,27 +192,31 @@ __device__ __forceinline__ void reg_update_generic(uint32_t e, const ModConst &m
 
 // The full words (positions kMaxW - W .. kMaxW - 2) with the word shape
 // (residues per word, bits per residue) known at compile time: the shape is
-// dispatched once per gate, not once per word.
-template <bool ACC, bool TAB, int NR, int BB>
-__device__ __forceinline__ void reg_full_words(const ModConst &mm, uint32_t coeff, const uint32_t (&D)[kMaxW],
-                                               const uint32_t (&row)[kMaxW], uint32_t (&T)[kMaxW], uint32_t tk) {
+// dispatched once per gate, not once per word.  D[p] becomes the word's
+// result (fast_word_c).
+template <bool TAB, int NR, int BB>
+__device__ __forceinline__ void reg_full_words(const ModConst &mm, uint32_t cc, uint32_t (&D)[kMaxW],
+                                               const uint32_t (&row)[kMaxW], const uint32_t (&T)[kMaxW], uint32_t lmask,
+                                               uint32_t km, uint64_t tk) {
     const uint32_t off = label_off(mm);
     static_for<kMaxW - 1>([&](auto p) {
-        if (p >= static_cast<int>(off)) {
-            T[p] = fast_word_c<ACC, NR, BB, TAB>(D[p], mm.lo_M_f, mm.lo_s_f, mm.pw_lo_f, mm.fc_hi_f, mm.fc_lo_f, row[p],
-                                                 T[p], coeff, mm, tk);
+        if (p > 0 || off == 0) {  // five or six words (fill_mod_const)
+            D[p] = fast_word_c<NR, BB, TAB>(D[p], mm.lo_M_f, mm.lo_s_f, mm.pw_lo_f, mm.fc_hi_f, mm.fc_lo_f, row[p],
+                                            T[p], lmask, km, cc, mm, tk);
         }
     });
 }
 
-template <bool ACC, bool TAB>
-__device__ __forceinline__ void reg_update_fast(uint32_t e, const ModConst &mm, const uint32_t (&D)[kMaxW],
-                                                const uint32_t (&row)[kMaxW], uint32_t (&T)[kMaxW], uint32_t tk) {
-    const uint32_t coeff = eg_coeff(e);
+template <bool TAB>
+__device__ __forceinline__ void reg_update_fast(uint32_t e, const ModConst &mm, uint32_t (&D)[kMaxW],
+                                                const uint32_t (&row)[kMaxW], uint32_t (&T)[kMaxW], uint64_t tk) {
+    const bool acc = eg_kind(e) != 0;
+    const uint32_t cc = acc ? eg_coeff(e) : mm.m - eg_coeff(e);  // c' (the coefficient is in 1..m-1)
+    const uint32_t lmask = opaque(acc ? 0u : 0xffffffffu), km = opaque(acc ? 0u : mm.sw_ones * mm.m);
     // full words: g = floor(32 / b) residues of b bits
     switch (mm.fd ? mm.g | (mm.b << 8) : 0u) {
 #define REDASH_FULL(NR, BB) \
-    case (NR) | ((BB) << 8): reg_full_words<ACC, TAB, NR, BB>(mm, coeff, D, row, T, tk); break;
+    case (NR) | ((BB) << 8): reg_full_words<TAB, NR, BB>(mm, cc, D, row, T, lmask, km, tk); break;
         REDASH_FULL(16, 2) REDASH_FULL(10, 3) REDASH_FULL(8, 4) REDASH_FULL(6, 5) REDASH_FULL(5, 6)
         REDASH_FULL(4, 7) REDASH_FULL(4, 8)
 #undef REDASH_FULL
@@ -216,22 +224,26 @@ __device__ __forceinline__ void reg_update_fast(uint32_t e, const ModConst &mm, 
             const uint32_t off = label_off(mm);
             static_for<kMaxW - 1>([&](auto p) {
                 if (p >= static_cast<int>(off)) {
-                    T[p] = fast_word<ACC>(D[p], mm.g, mm.nlo_f, mm.lo_M_f, mm.lo_s_f, mm.pw_lo_f, row[p], T[p], coeff,
-                                          mm);
+                    D[p] = fast_word(D[p], mm.g, mm.nlo_f, mm.lo_M_f, mm.lo_s_f, mm.pw_lo_f, row[p], T[p], acc, cc, mm);
                 }
             });
         }
     }
-    T[kMaxW - 1] = fast_word_any<ACC, TAB>(D[kMaxW - 1], mm.glast, mm.nlo_l, mm.lo_M_l, mm.lo_s_l, mm.pw_lo_l, mm.fc_hi_l,
-                                           mm.fc_lo_l, row[kMaxW - 1], T[kMaxW - 1], coeff, mm, tk);
+    D[kMaxW - 1] = fast_word_any<TAB>(D[kMaxW - 1], mm.glast, mm.nlo_l, mm.lo_M_l, mm.lo_s_l, mm.pw_lo_l, mm.fc_hi_l,
+                                      mm.fc_lo_l, row[kMaxW - 1], T[kMaxW - 1], lmask, km, acc, cc, mm, tk);
+    if (acc) {
+        const uint32_t E = opaque(mm.sw_even);
+        static_for<kMaxW>([&](auto p) { T[p] = swar_add(T[p], D[p] & E, (D[p] >> mm.b) & E, mm); });
+    } else {
+        static_for<kMaxW>([&](auto p) { T[p] = D[p]; });
+    }
 }
 
 // Applies gate g's free operation to the register label T: E = row + pad,
 // then L <- c (L - E) (sub: division step and the recursion of Eq.
 // rns_to_mrs) or L <- L + c E (acc: the mixed-radix recombination onto a
-// scaling modulus).  For an output modulus m <= 42 the product c (v mod m)
-// mod m comes from the gate's byte table in LDS: a sub gate's new residue is
-// T[l + 2m - p - r], an acc gate's is l + T[p + r] reduced once.
+// scaling modulus).  For an output modulus m <= 42 the products c' y mod m
+// (fast_word) come from the gate's byte table in LDS.
 // D: the gate's pad (pad_words_top, pad_words_all).
 __device__ __forceinline__ void reg_update(uint32_t g, uint32_t e, const ModConst &mm, uint32_t (&D)[kMaxW],
                                            uint32_t (&row)[kMaxW], uint32_t (&T)[kMaxW]) {
@@ -241,18 +253,9 @@ __device__ __forceinline__ void reg_update(uint32_t g, uint32_t e, const ModCons
             static_for<4>([&](auto w) { T[w + 2] ^= D[w + 2] ^ row[w + 2]; });
         }
     } else if (eg_tab(e)) {
-        const uint32_t tk = kEvalTableBase + g * kTableBytes + (eg_kind(e) ? 0u : mm.two_m);
-        if (eg_kind(e)) {
-            reg_update_fast<true, true>(e, mm, D, row, T, tk);
-        } else {
-            reg_update_fast<false, true>(e, mm, D, row, T, tk);
-        }
+        reg_update_fast<true>(e, mm, D, row, T, opaque64(static_cast<uint64_t>(kEvalTableBase + g * kTableBytes) << 32));
     } else if (mm.fast) {
-        if (eg_kind(e)) {
-            reg_update_fast<true, false>(e, mm, D, row, T, 0);
-        } else {
-            reg_update_fast<false, false>(e, mm, D, row, T, 0);
-        }
+        reg_update_fast<false>(e, mm, D, row, T, 0);
     } else {
         reg_update_generic(e, mm, D, row, T);
     }
@@ -265,13 +268,8 @@ __device__ __forceinline__ void stage_free_op_tables_e(const EvalPlan &P, uint32
     for (uint32_t g = wave; g < P.ntab; g += nwaves) {
         const uint32_t e = P.egate[g];
         if (!eg_tab(e) || lane >= kTableBytes / 4) continue;
-        const uint32_t m = P.mod[eg_dst(e)].m, c = eg_coeff(e);
-        uint32_t w = 0;
-        for (uint32_t k = 0; k < 4; ++k) {
-            const uint32_t v = 4 * lane + k;
-            w |= ((c * (v % m)) % m) << (8 * k);
-        }
-        lds[(kEvalTableBase + g * kTableBytes) / 4 + lane] = w;
+        lds[(kEvalTableBase + g * kTableBytes) / 4 + lane] =
+            free_op_entries(lane, eg_kind(e), eg_coeff(e), P.mod[eg_dst(e)].m);
     }
 }
 
