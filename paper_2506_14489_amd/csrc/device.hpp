@@ -54,6 +54,13 @@ __device__ __forceinline__ uint32_t opaque(uint32_t v) {
     return v;
 }
 
+// The same, computed anew at every use: a value made from it is not kept in a
+// register from one use to the next.
+__device__ __forceinline__ uint32_t opaque_here(uint32_t v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 __device__ __forceinline__ uint64_t opaque64(uint64_t v) {
     asm("" : "+v"(v));
     return v;
@@ -115,7 +122,8 @@ struct FourTables {
 // copy c at byte 4c of each half.  Lane l reads copy l mod 32, which sits in
 // bank l mod 32: a wavefront's lookups never conflict, whatever the indices.
 // One v_perm_b32 builds the address 256 x + 4 (l mod 32) (+ 128 for TE2)
-// straight from the state word.  Since TE1 = rotl8 TE0 and TE3 = rotl8 TE2,
+// straight from the state word (for byte 1 an and-or);
+// TE2's half is an immediate offset of the read.  Since TE1 = rotl8 TE0 and TE3 = rotl8 TE2,
 // a column is TE0[a] ^ TE2[c] ^ rotl8(TE0[b] ^ TE2[d] ^ rotr8(k)): two
 // three-input XORs and one rotation.
 constexpr int kReplicas = 32;
@@ -138,24 +146,31 @@ __device__ __forceinline__ uint32_t lds_read_u8(uint32_t addr) {
 }
 
 struct PermTE02 {
-    uint32_t off0, off2;  // 4 (lane mod 32), and that + 128
-    // address bytes: [offset, byte k of w, 0, 0]
-    __device__ __forceinline__ static uint32_t at(uint32_t w, uint32_t off, int k) {
-        return lds_read(__builtin_amdgcn_perm(w, off, 0x0c0c0000u | ((4u + k) << 8)));
+    uint32_t off;    // 4 (lane mod 32)
+    uint32_t byte1;  // 0xff00
+    // The row address of byte k of w, address bytes [off, byte, 0, 0]; TE2's
+    // half is the read's immediate offset.  Byte 1 is in place: an and-or,
+    // which takes half as long as a byte permute (with its mask in a vector
+    // register).
+    __device__ __forceinline__ uint32_t row(uint32_t w, int k) const {
+        if (k == 1) return __builtin_amdgcn_bitop3_b32(w, byte1, off, 0xea);
+        return __builtin_amdgcn_perm(w, off, 0x0c0c0000u | ((4u + k) << 8));
     }
+    __device__ __forceinline__ uint32_t te0(uint32_t w, int k) const { return lds_read(row(w, k)); }
+    __device__ __forceinline__ uint32_t te2(uint32_t w, int k) const { return lds_read(row(w, k) + kTableRowBytes / 2); }
     template <typename Key>
     __device__ __forceinline__ uint32_t column(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, const Key &K,
                                                int i) const {
-        return xor3(at(w0, off0, 0), at(w2, off2, 2), rotl8(xor3(at(w1, off0, 1), at(w3, off2, 3), K.rot(i))));
+        return xor3(te0(w0, 0), te2(w2, 2), rotl8(xor3(te0(w1, 1), te2(w3, 3), K.rot(i))));
     }
     // A round of two blocks whose inputs differ in bit 0 of w[0] only: of the
     // 16 lookups one differs (byte 0 of w[0], row x ^ 1), and it enters column
     // 0 only.  c: block 0's columns; the return value is block 1's column 0.
     template <typename Key>
     __device__ __forceinline__ uint32_t first_round_pair(const uint32_t (&w)[4], const Key &K, uint32_t (&c)[4]) const {
-        const uint32_t p = __builtin_amdgcn_perm(w[0], off0, 0x0c0c0400u);
+        const uint32_t p = row(w[0], 0);
         const uint32_t a = lds_read(p), a1 = lds_read(p ^ kTableRowBytes);
-        c[0] = xor3(a, at(w[2], off2, 2), rotl8(xor3(at(w[1], off0, 1), at(w[3], off2, 3), K.rot(4))));
+        c[0] = xor3(a, te2(w[2], 2), rotl8(xor3(te0(w[1], 1), te2(w[3], 3), K.rot(4))));
         c[1] = column(w[1], w[2], w[3], w[0], K, 5);
         c[2] = column(w[2], w[3], w[0], w[1], K, 6);
         c[3] = column(w[3], w[0], w[1], w[2], K, 7);
@@ -166,12 +181,12 @@ struct PermTE02 {
     template <typename Key>
     __device__ __forceinline__ void second_round_pair(const uint32_t (&c)[4], uint32_t c01, const Key &K,
                                                       uint32_t (&d)[4], uint32_t (&d1)[4]) const {
-        const uint32_t a0 = at(c[0], off0, 0), b0 = at(c[0], off0, 1), e0 = at(c[0], off2, 2), f0 = at(c[0], off2, 3);
-        const uint32_t a1 = at(c01, off0, 0), b1 = at(c01, off0, 1), e1 = at(c01, off2, 2), f1 = at(c01, off2, 3);
-        d[0] = xor3(a0, at(c[2], off2, 2), rotl8(xor3(at(c[1], off0, 1), at(c[3], off2, 3), K.rot(8))));
-        d[1] = xor3(at(c[1], off0, 0), at(c[3], off2, 2), rotl8(xor3(at(c[2], off0, 1), f0, K.rot(9))));
-        d[2] = xor3(at(c[2], off0, 0), e0, rotl8(xor3(at(c[3], off0, 1), at(c[1], off2, 3), K.rot(10))));
-        d[3] = xor3(at(c[3], off0, 0), at(c[1], off2, 2), rotl8(xor3(b0, at(c[2], off2, 3), K.rot(11))));
+        const uint32_t a0 = te0(c[0], 0), b0 = te0(c[0], 1), e0 = te2(c[0], 2), f0 = te2(c[0], 3);
+        const uint32_t a1 = te0(c01, 0), b1 = te0(c01, 1), e1 = te2(c01, 2), f1 = te2(c01, 3);
+        d[0] = xor3(a0, te2(c[2], 2), rotl8(xor3(te0(c[1], 1), te2(c[3], 3), K.rot(8))));
+        d[1] = xor3(te0(c[1], 0), te2(c[3], 2), rotl8(xor3(te0(c[2], 1), f0, K.rot(9))));
+        d[2] = xor3(te0(c[2], 0), e0, rotl8(xor3(te0(c[3], 1), te2(c[1], 3), K.rot(10))));
+        d[3] = xor3(te0(c[3], 0), te2(c[1], 2), rotl8(xor3(b0, te2(c[2], 3), K.rot(11))));
         d1[0] = xor3(d[0], a0, a1);
         d1[1] = d[1] ^ rotl8(f0 ^ f1);
         d1[2] = xor3(d[2], e0, e1);
@@ -181,8 +196,8 @@ struct PermTE02 {
     __device__ __forceinline__ uint32_t last_column(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, const Key &K,
                                                     int i) const {
         // S(x) is byte 1 and byte 2 of TE0[x], byte 0 and byte 3 of TE2[x]
-        const uint32_t lo = __builtin_amdgcn_perm(at(w1, off0, 1), at(w0, off2, 0), 0x0c0c0500u);
-        const uint32_t hi = __builtin_amdgcn_perm(at(w3, off2, 3), at(w2, off0, 2), 0x07020c0cu);
+        const uint32_t lo = __builtin_amdgcn_perm(te0(w1, 1), te2(w0, 0), 0x0c0c0500u);
+        const uint32_t hi = __builtin_amdgcn_perm(te2(w3, 3), te0(w2, 2), 0x07020c0cu);
         return xor3(lo, hi, K(i));
     }
 };
@@ -197,7 +212,7 @@ __device__ __forceinline__ void stage_perm_te02(uint32_t *lds, int tid, int nthr
 
 __device__ __forceinline__ PermTE02 perm_te02() {
     const uint32_t off = 4u * (threadIdx.x % kReplicas);
-    return PermTE02{off, off + 128u};
+    return PermTE02{off, opaque(0xff00u)};
 }
 
 // NB independent blocks encrypted round by round, so that the table reads of
@@ -757,7 +772,7 @@ __device__ __forceinline__ void hash_fraction_n(const Tab &T, const Key &rk, uin
 
 // The two-block hashes of NG gates, the AES blocks of all of them round by
 // round.  x: the folded input label that the gates share, gate j under tweak
-// tau + j; V[j] receives the 256-bit fraction: limbs 0-3 are the output words
+// tweak() + j (called before and after the rounds); V[j] receives the 256-bit fraction: limbs 0-3 are the output words
 // of block 0, 4-7 of block 1.
 //
 // The two blocks of a hash differ in bit 0 of word 0 alone (4 tau and 4 tau +
@@ -766,10 +781,11 @@ __device__ __forceinline__ void hash_fraction_n(const Tab &T, const Key &rk, uin
 // through a carry (see pad_words_top), and without `all` they are not
 // computed (3 of block 0's 4 last-round columns).  Per hash 281 lookups
 // instead of 320.
-template <int NG, bool PAIRED = false, typename Key>
-__device__ __forceinline__ void hash_pairs(const PermTE02 &T, const Key &K, const uint32_t (&x)[4], uint64_t tau,
+template <int NG, typename Key, typename Tweak>
+__device__ __forceinline__ void hash_pairs(const PermTE02 &T, const Key &K, const uint32_t (&x)[4], Tweak &&tweak,
                                            uint32_t gid, bool all, uint32_t (&V)[NG][8]) {
     uint32_t s[2 * NG][4];
+    const uint64_t tau = tweak();
     __builtin_amdgcn_s_setprio(1);  // as in aes128_encrypt_n
 #pragma unroll
     for (int j = 0; j < NG; ++j) {
@@ -783,7 +799,10 @@ __device__ __forceinline__ void hash_pairs(const PermTE02 &T, const Key &K, cons
         T.second_round_pair(c, c01, K, s[2 * j], s[2 * j + 1]);
         __builtin_amdgcn_sched_barrier(0);
     }
-    // Rounds 3..9 stay a loop, as in aes128_encrypt_n (PAIRED likewise).
+    // Rounds 3..9 stay a loop (the instruction cache then holds the gate loop),
+    // three rounds a pass: a block's new state needs four registers of its own
+    // while the old one is read, and after three rounds of two blocks over
+    // three register sets every state is back where it began, without copies.
     auto round_to = [&](const uint32_t(&in)[2 * NG][4], uint32_t(&o)[2 * NG][4], int r) {
 #pragma unroll
         for (int b = 0; b < 2 * NG; ++b) {
@@ -812,27 +831,20 @@ __device__ __forceinline__ void hash_pairs(const PermTE02 &T, const Key &K, cons
             V[j][7] = T.last_column(b3, b0, b1, b2, K, 43);
         }
     };
-    if constexpr (PAIRED) {
-        uint32_t t[2 * NG][4];
 #pragma unroll 1
-        for (int r = 3; r < 9; r += 2) {
-            round_to(s, t, r);
-            round_to(t, s, r + 1);
-        }
-        round_to(s, t, 9);
-        last_round(t);
-    } else {
-#pragma unroll 1
-        for (int r = 3; r < 10; ++r) round_to(s, s, r);
-        last_round(s);
+    for (int r = 3; r < 9; r += 3) {
+        round_to(s, s, r);
+        round_to(s, s, r + 1);
+        round_to(s, s, r + 2);
     }
+    round_to(s, s, 9);
+    last_round(s);
     __builtin_amdgcn_s_setprio(0);
     // Matyas-Meyer-Oseas feed-forward of the block input u ^ T.  The inputs
     // are formed again from x and tau rather than kept through the rounds
     // (opaque keeps the compiler from reusing the earlier values).
     const uint32_t y0 = opaque(x[0]), y1 = opaque(x[1]), y2 = opaque(x[2]), y3 = opaque(x[3]);
-    const uint64_t tau2 = (static_cast<uint64_t>(opaque(static_cast<uint32_t>(tau >> 32))) << 32) |
-                          opaque(static_cast<uint32_t>(tau));
+    const uint64_t tau2 = tweak();
 #pragma unroll
     for (int j = 0; j < NG; ++j) {
         const uint64_t tw = (tau2 + static_cast<uint64_t>(j)) * 4u;

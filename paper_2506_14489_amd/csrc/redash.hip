@@ -38,13 +38,20 @@ constexpr uint32_t eval_lds_bytes(uint32_t ntab) { return kEvalTableBase + ntab 
 static_assert(kLdsKeyWords * 4 <= 384, "round keys overlap the free-operation tables");
 static_assert(2 * (kEvalTableBase + kMaxTables * kTableBytes) <= 160 * 1024, "two workgroups per CU");
 static_assert(sizeof(EvalPlan) <= 4096, "the evaluator's plan is passed as its kernel argument block");
-// Two workgroups of 768 threads share a CU (2 x 64.3 KiB of LDS): six waves
-// per SIMD, which caps the kernel at 80 VGPRs.
+// The split evaluator: two workgroups of 768 threads share a CU (2 x 64.3 KiB
+// of LDS), six waves per SIMD, which caps the kernel at 80 VGPRs.
 constexpr int kEvalBlock = 768;
 constexpr int kEvalWaves = 6;
-// The one-gadget-per-lane evaluator k_eval: workgroup size and waves per SIMD.
-constexpr int kLaneBlock = 768;
-constexpr int kLaneWaves = 6;
+// The one-gadget-per-lane evaluator k_eval: two workgroups of 1024, eight
+// waves per SIMD at 64 VGPRs.  It is bound by the LDS pipe (25,800 table reads
+// a wave, two cycles each) and the vector ALU together; what a wave waits for
+// (reads of a round, rows) only other waves can fill, and eight waves with one
+// gate hashed at a time beat six with two gates' blocks interleaved (80 VGPRs)
+// and four on unrotated tables (128 KiB of them, 16 vector instructions fewer
+// per round): 7.0, 7.5 and 8.0 ms at 3,211,264 gadgets of 77 gates.  A spill
+// costs more than it moves: its reload waits for the row in flight.
+constexpr int kLaneBlock = 1024;
+constexpr int kLaneWaves = 8;
 // The garbler: the same LDS image without the free-operation tables; two
 // workgroups of 512 per CU, four waves per SIMD (up to 128 VGPRs).
 constexpr int kGarbleBlock = 512;
@@ -102,8 +109,8 @@ __device__ __forceinline__ void stage_free_op_tables(const Plan &P, uint32_t *ld
 // ---------------------------------------------------------------------------
 // The one-gadget-per-lane evaluator, target-major (EvalPlan): a block's two
 // target labels stay in registers from their first gate to their last, so
-// each is read and written once; a step hashes one digit label for one gate
-// of each slot (four AES blocks interleaved) or for one slot.  Updates always
+// each is read and written once; a step folds one digit label for one gate
+// of each slot or for one slot, and takes its gates in turn.  Updates always
 // act on slot 0: slot 1 is brought there by swapping the two slots.
 // ---------------------------------------------------------------------------
 
@@ -141,6 +148,19 @@ __device__ __forceinline__ void store_label(const uint32_t (&T)[kMaxW], const La
     static_for<kMaxW>([&](auto p) {
         if (p >= static_cast<int>(off)) LB.put(b, p - off, T[p]);
     });
+}
+
+// A row of W words (4, 5 or 6, word-aligned), right-aligned like the labels:
+// its last four words in one load.
+__device__ __forceinline__ void load_row(uint32_t (&row)[kMaxW], const uint32_t *__restrict__ rp, uint32_t W) {
+    typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(4)));
+    const u4 v = *reinterpret_cast<const u4 *>(rp + (W - 4));
+    row[2] = v.x;
+    row[3] = v.y;
+    row[4] = v.z;
+    row[5] = v.w;
+    if (W > 4) row[1] = rp[W - 5];
+    if (W > 5) row[0] = rp[0];
 }
 
 // XOR-fold of a right-aligned register label with OFF = kMaxW - W: word w
@@ -296,48 +316,16 @@ __device__ __forceinline__ void gate_pad(const PermTE02 &TT, const uint32_t *K, 
     pad_words_all(V, mm, D);
 }
 
-// One step's NG gates g, g+1 (NG = 2) or g: requests their rows (the colour
-// is known before hashing), then runs the 2 NG AES blocks interleaved.
-//
-// The gadget index a (below 2^30) is a 32-bit register: the row offset
-// a (q-1) W + (c-1) W and the tweak (a0 + a) G + g are each one
-// 32 x 32 + 64-bit multiply-add from it, instead of 64-bit values kept live
-// across the whole gadget.
+// The gadget index a (below 2^30) is a 32-bit value: the row offset
+// a (q-1) W + (c-1) W and the tweak (a0 + a) G + g are each 32 x 32 + 64-bit
+// multiply-adds from it, instead of 64-bit values kept live across the gadget.
 __device__ __forceinline__ uint64_t mad64(uint32_t x, uint32_t y, uint64_t z) {
     return static_cast<uint64_t>(x) * y + z;
 }
 
 // Gate g's tweak for local gadget a.
 __device__ __forceinline__ uint64_t gate_tweak(const EvalPlan &P, uint32_t a, uint32_t g) {
-    return mad64(opaque(a), P.G, P.a0 * P.G + g);
-}
-
-template <int NG>
-__device__ __forceinline__ void step_hash(const EvalPlan &P, uint32_t g, uint32_t q, const uint32_t (&x)[4],
-                                          uint32_t colour, const PermTE02 &TT, const uint32_t *K, uint32_t a,
-                                          const uint32_t *__restrict__ tab, uint32_t (&V)[2][8],
-                                          uint32_t (&row)[2][kMaxW]) {
-    static_for<NG>([&](auto j) {
-        const uint32_t e = P.egate[g + j];
-        const uint32_t Wd = P.mod[eg_dst(e)].W;
-        static_for<kMaxW>([&](auto w) { row[j][w] = 0; });
-        if (colour != 0) {  // right-aligned like the labels
-            const uint32_t *rp = tab + static_cast<uint64_t>(eg_toff(e)) * P.n +
-                                 mad64(opaque(a), (q - 1) * Wd, static_cast<uint64_t>(colour - 1) * Wd);
-            const int off = kMaxW - static_cast<int>(Wd);
-            static_for<kMaxW>([&](auto p) {
-                if (p >= off) row[j][p] = rp[p - off];
-            });
-        }
-    });
-    bool all = false;
-    static_for<NG>([&](auto j) { all = all || P.mod[eg_dst(P.egate[g + j])].pad_amb == 0; });
-    uint32_t Vn[NG][8];
-    hash_pairs<NG>(TT, LdsKey{K}, x, gate_tweak(P, a, g), P.gid, all, Vn);
-    // (a single gate clears the second's, which would otherwise be carried
-    // from step to step in registers)
-    static_for<2>([&](auto j) { static_for<8>([&](auto l) { V[j][l] = j < NG ? Vn[j < NG ? j : 0][l] : 0u; }); });
-    if constexpr (NG == 1) static_for<kMaxW>([&](auto w) { row[1][w] = 0; });
+    return mad64(a, P.G, P.a0 * P.G + g);
 }
 
 template <int BLOCK>
@@ -353,9 +341,10 @@ k_eval(const EvalPlan P, const uint32_t *__restrict__ in, const uint32_t *__rest
     stage_free_op_tables_e(P, lds, tid, static_cast<uint32_t>(nthr) / 64u);
     __syncthreads();
     const PermTE02 TT = perm_te02();
-    const uint32_t a = blockIdx.x * static_cast<uint32_t>(nthr) + static_cast<uint32_t>(tid);  // n < 2^30
-    if (a >= P.n) return;  // no barrier follows
-    const LabelBufs LB{in, out, work, P.n, a * 4u};
+    const uint32_t a0 = blockIdx.x * static_cast<uint32_t>(nthr) + static_cast<uint32_t>(tid);  // n < 2^30
+    if (a0 >= P.n) return;  // no barrier follows
+    // (only the byte offset 4 a stays in a register)
+    const LabelBufs LB{in, out, work, P.n, opaque(a0 * 4u)};
 
     for (uint32_t b = 0; b < P.nblocks; ++b) {
         const uint32_t bd = P.block[b];
@@ -376,20 +365,22 @@ k_eval(const EvalPlan P, const uint32_t *__restrict__ in, const uint32_t *__rest
             const uint32_t q = mq.m;
             auto digit = [&](uint32_t(&x)[4]) -> uint32_t {
                 static_for<4>([&](auto l) { x[l] = 0; });
-                uint32_t w0;
-                if (st_dloc(sd) == kDigSlot0) {  // the block's first target, now in T[1]
-                    switch (label_off(mq)) {
+                uint32_t w0, W = mq.W, loc = st_dloc(sd);
+                // (kept here: for the rare second use nothing is computed ahead)
+                asm volatile("" : "+s"(W), "+s"(loc));
+                if (loc == kDigSlot0) {  // the block's first target, now in T[1]
+                    switch (kMaxW - W) {
                         case 0: fold_regs<0>(T[1], x); w0 = T[1][0]; break;
                         case 1: fold_regs<1>(T[1], x); w0 = T[1][1]; break;
                         default: fold_regs<2>(T[1], x); w0 = T[1][2]; break;
                     }
                 } else {
-                    const uint32_t *dig = LB.base(st_dloc(sd), mq);
+                    const uint32_t *dig = LB.base(loc, mq);
                     w0 = LB.get(dig, 0);
                     x[0] = w0;
                     static_for<kMaxW - 1>([&](auto w1) {
                         constexpr int w = decltype(w1)::value + 1;
-                        if (w < static_cast<int>(mq.W)) x[w & 3] ^= LB.get(dig, w);
+                        if (w < static_cast<int>(W)) x[w & 3] ^= LB.get(dig, w);
                     });
                 }
                 return w0;
@@ -399,27 +390,29 @@ k_eval(const EvalPlan P, const uint32_t *__restrict__ in, const uint32_t *__rest
             uint32_t colour = w0 & mq.mask;
             if (colour >= q) colour = 0;
             const uint32_t g = st_gate(sd);
-            uint32_t V[2][8], row[2][kMaxW];
-            if (two) {
-                step_hash<2>(P, g, q, x, colour, TT, K, a, tab, V, row);
-            } else {
-                step_hash<1>(P, g, q, x, colour, TT, K, a, tab, V, row);
-            }
-            // one copy of the update code: gate j acts on slot 0, then the
-            // slots (and the gate's pad and row) move along
             const uint32_t ng = two ? 2u : 1u;
 #pragma unroll 1
             for (uint32_t j = 0; j < ng; ++j) {
-                const uint32_t e = P.egate[g + j];
-                const ModConst mm = P.mod[eg_dst(e)];
-                uint32_t D[kMaxW];
-                gate_pad(TT, K, P.gid, mm, V[0], D, digit, [&] { return gate_tweak(P, a, g + j); });
-                reg_update(g + j, e, mm, D, row[0], T[0]);
-                if (two) {
-                    swap_slots(T);
-                    static_for<8>([&](auto l) { V[0][l] = V[1][l]; });
-                    static_for<kMaxW>([&](auto w) { row[0][w] = row[1][w]; });
+                uint32_t e = P.egate[g + j];
+                uint32_t row[kMaxW], V[1][8], D[kMaxW];
+                static_for<kMaxW>([&](auto w) { row[w] = 0; });
+                {
+                    const uint32_t W = P.mod[eg_dst(e)].W;
+                    if (colour != 0) {
+                        // row (colour - 1) of the gadget's q - 1
+                        const uint64_t at = static_cast<uint64_t>(eg_toff(e)) * P.n - W;
+                        load_row(row, tab + mad64(opaque(colour), W, mad64(opaque(LB.aoff) >> 2, (q - 1) * W, at)), W);
+                    }
+                    hash_pairs<1>(TT, LdsKey{K}, x, [&] { return gate_tweak(P, opaque_here(LB.aoff) >> 2, g + j); }, P.gid,
+                                  P.mod[eg_dst(e)].pad_amb == 0, V);
                 }
+                // (the modulus's constants are loaded here, not held in scalar
+                // registers through the hash)
+                asm volatile("" : "+s"(e));
+                const ModConst mm = P.mod[eg_dst(e)];
+                gate_pad(TT, K, P.gid, mm, V[0], D, digit, [&] { return gate_tweak(P, opaque(LB.aoff) >> 2, g + j); });
+                reg_update(g + j, e, mm, D, row, T[0]);
+                if (two) swap_slots(T);
             }
             if (alone1) swap_slots(T);
             const uint32_t f = st_store(sd);
@@ -509,17 +502,11 @@ k_eval_split(const Plan P, const uint32_t *__restrict__ in, const uint32_t *__re
                 // the row (right-aligned, as the register labels)
                 uint32_t row[kMaxW];
                 static_for<kMaxW>([&](auto p) { row[p] = 0; });
-                if (colour != 0) {
-                    const uint32_t *rp = tab + toff + (a * (q - 1) + (colour - 1)) * Wd;
-                    const int off = kMaxW - static_cast<int>(Wd);
-                    static_for<kMaxW>([&](auto p) {
-                        if (p >= off) row[p] = rp[p - off];
-                    });
-                }
+                if (colour != 0) load_row(row, tab + toff + (a * (q - 1) + (colour - 1)) * Wd, Wd);
                 uint32_t T[kMaxW];
                 load_label(T, LB, gate_tsrc(d), mm, gate_tsrc(d) != kLocZero);
                 uint32_t Vn[1][8], D[kMaxW];
-                hash_pairs<1, true>(TT, LdsKey{K}, x, tau0 + g + i, P.gid, mm.pad_amb == 0, Vn);
+                hash_pairs<1>(TT, LdsKey{K}, x, [&] { return opaque64(tau0 + g + i); }, P.gid, mm.pad_amb == 0, Vn);
                 gate_pad(TT, K, P.gid, mm, Vn[0], D,
                          [&](uint32_t(&f)[4]) { static_for<4>([&](auto l) { f[l] = x[l]; }); },
                          [&] { return tau0 + g + i; });
@@ -1107,10 +1094,16 @@ uint32_t split_for(uint64_t count, uint64_t cus) {
 // 64 gadgets after the round's: they take the CUs the round frees first,
 // instead of adding a wave to some SIMDs for the whole call.  A larger call
 // runs on k_eval, one gadget per lane: whole rounds of two full workgroups per
-// CU, and a rest that the 12-wave split holds in one round goes to it after
-// them instead of running as a last round with few waves per SIMD, whose
-// gadgets would take the latency of their gate chain (a larger rest costs
-// k_eval no more than it would cost the split).
+// CU, and a rest that the 12- or 4-wave split holds in one round goes to it
+// after them instead of running as a last round with few waves per SIMD, whose
+// gadgets would take the latency of their gate chain (12 primes: 3,211,264
+// gadgets, 65,536 over six rounds, 7.35 -> 7.00 ms; 622,592 1.57 -> 1.46; a
+// rest of 175,712 costs the same either way).  A chain of few gates is short
+// enough as it is (5 gates, 65,536 over: 0.558 ms against 0.570).  A larger
+// rest over one round makes two even rounds of smaller workgroups: a CU whose
+// two workgroups end together would otherwise take two full ones of the rest
+// and another CU none (802,816 gadgets 2.12 -> 1.90 ms; no gain from three
+// rounds on).
 int launch_eval(const Plan &P, uint32_t lds, const uint32_t *in, const uint32_t *tab, uint32_t *out, uint32_t *work,
                 hipStream_t stream) {
     DeviceInfo d;
@@ -1132,10 +1125,10 @@ int launch_eval(const Plan &P, uint32_t lds, const uint32_t *in, const uint32_t 
     const uint64_t round = 2 * ncu * kLaneBlock;  // gadgets of one round, one per lane
     uint64_t bulk = P.n;
     const uint64_t rest = P.n % round;
-    if (P.n > round && rest > 0 && rest <= 2 * ncu * 64) bulk = P.n - rest;
+    if (P.n > round && rest > 0 && rest <= (P.G >= 16 ? 2 * ncu * split_most(4) : 2 * ncu * 64)) bulk = P.n - rest;
     if ((rc = allow_lds(reinterpret_cast<const void *>(&k_eval<kLaneBlock>), lds))) return rc;
     int block = 0;
-    if ((rc = block_for(bulk, kLaneBlock, &block))) return rc;
+    if ((rc = block_for(bulk > round && bulk < 2 * round ? (bulk + 1) / 2 : bulk, kLaneBlock, &block))) return rc;
     const EvalPlan &E = eval_plan(P);
     hipLaunchKernelGGL(k_eval<kLaneBlock>, dim3(grid_for(bulk, block)), dim3(block), lds, stream, E, in, tab, out,
                        work);

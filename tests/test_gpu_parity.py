@@ -563,6 +563,38 @@ def test_one_gadget_per_lane_on_varied_bases(name, moduli, S):
     _check_full(w, 2048, 2048, 2048, 8)
 
 
+# One gadget per lane: rounds of two 1,024-gadget workgroups per CU.  A rest of
+# up to 192 gadgets per workgroup of a round goes to the 12- and 4-wave splits
+# (64 on chains of fewer than 16 gates), a larger one over a single round
+# makes two even rounds.  (name, base, scaling, gadgets per workgroup of the
+# two per CU, extra)
+LANE_EDGES = [("round-last", tuple(WL.PRIMES_12), (11,), 1024, 0),
+              ("rest-split4-first", tuple(WL.PRIMES_12), (11,), 1024 + 64, 1),
+              ("rest-split4-last", tuple(WL.PRIMES_12), (10, 11), 1024 + 192, 0),
+              ("even-halves-first", tuple(WL.PRIMES_12), (11,), 1024 + 192, 1),
+              ("even-halves-ragged", tuple(WL.PRIMES_12[:8]), (2,), 2047, 63),
+              ("two-rounds-rest", (3, 5, 7, 8, 11, 13, 17, 19), (3,), 2048 + 100, 7),
+              ("few-gates-rest", (32, 97, 107), (0,), 1024 + 64, 1)]
+
+
+@pytest.mark.parametrize("name,moduli,S,per,extra", LANE_EDGES, ids=[e[0] for e in LANE_EDGES])
+def test_one_gadget_per_lane_rounds(name, moduli, S, per, extra):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    P = rns.cardinality(moduli)
+    w = WL.Workload(f"lane-{name}", tuple(moduli), tuple(S), 2 * cus * per + extra, 100 + per + extra, "uniform",
+                    -(P // 2), P - P // 2)
+    _check_full(w, 2048, 2048, 4096, 8)
+
+
+@pytest.mark.parametrize("name,moduli,S", K_EVAL_BASES, ids=[b[0] for b in K_EVAL_BASES])
+def test_one_gadget_per_lane_past_the_round_and_rest_on_varied_bases(name, moduli, S):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    P = rns.cardinality(moduli)
+    w = WL.Workload(f"lane-{name}", tuple(moduli), tuple(S), 2 * cus * 384 + cus * 64 + 1, 70 + len(moduli), "uniform",
+                    -(P // 2), P - P // 2)
+    _check_full(w, 2048, 2048, 2048, 8)
+
+
 RANDOM_LANE_BASES = [c[:3] for c in _random_bases(4, 7207)]
 
 
