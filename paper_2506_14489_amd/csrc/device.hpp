@@ -608,16 +608,12 @@ __device__ __forceinline__ uint32_t fast_word_any(uint32_t D, uint32_t nres, uin
     }
 }
 
-// Garbler rows: for one packed word over Z_m (m > 2, fast constants), the
-// residues (b_j - p_j) mod m, where p_j are the word's pad digits held in D
-// as a base-m number (residue 0 the most significant digit) and b_j the
-// residues of the packed word bw.
+// The digits of one packed word's pad (D as a base-m number, residue 0 the
+// most significant digit) in their fields, shape known at compile time.
 template <int NRES, int B>
-__device__ __forceinline__ uint32_t row_word_c(uint32_t D, uint32_t lo_M, uint32_t lo_s, uint32_t pw_lo, uint32_t c_hi,
-                                               uint32_t c_lo, uint32_t bw, const ModConst &mc) {
+__device__ __forceinline__ uint32_t pack_word_c(uint32_t D, uint32_t lo_M, uint32_t lo_s, uint32_t pw_lo, uint32_t c_hi,
+                                                uint32_t c_lo, const ModConst &mc) {
     constexpr int NLO = NRES / 2, NHI = NRES - NLO;
-    constexpr uint32_t MASK = (1u << B) - 1u;
-    const uint32_t m = uniform24(mc.m);
     uint32_t hi = D, lo = 0;
     if constexpr (NLO > 0) {
         hi = __umulhi(D, lo_M) >> lo_s;
@@ -626,40 +622,62 @@ __device__ __forceinline__ uint32_t row_word_c(uint32_t D, uint32_t lo_M, uint32
     uint32_t res = 0;
     auto residue = [&](uint32_t p, auto jc) {
         constexpr int j = decltype(jc)::value;
-        const uint32_t d = ((bw >> (B * j)) & MASK) - p;
-        res |= umin(d, d + m) << (B * j);
+        res = j ? opaque(res | (p << (B * j))) : p;  // one shift-or each, as in fast_word_c
     };
     frac_digits<NHI, 0>(hi, c_hi, mc.m, 0u, residue);
     frac_digits<NLO, NHI>(lo, c_lo, mc.m, 0u, residue);
     return res;
 }
 
-// row_word_c for any word shape; shapes outside the unrolled list of
-// fast_word_any take the generic digit loop.
-__device__ __forceinline__ uint32_t row_word_any(uint32_t D, uint32_t nres, uint32_t lo_M, uint32_t lo_s,
-                                                 uint32_t pw_lo, uint32_t c_hi, uint32_t c_lo, uint32_t bw,
-                                                 const ModConst &mc) {
-    switch (mc.fd ? nres | (mc.b << 8) : 0u) {
+// pack_word_c for any word shape and any m > 2; shapes outside the unrolled
+// list of fast_word_any take the generic digit loop.
+__device__ __forceinline__ uint32_t pack_word_any(uint32_t D, uint32_t nres, uint32_t lo_M, uint32_t lo_s,
+                                                  uint32_t pw_lo, uint32_t c_hi, uint32_t c_lo, const ModConst &mc) {
+    switch (mc.fast && mc.fd ? nres | (mc.b << 8) : 0u) {
 #define REDASH_RW(NR, BB) \
-    case (NR) | ((BB) << 8): return row_word_c<NR, BB>(D, lo_M, lo_s, pw_lo, c_hi, c_lo, bw, mc);
+    case (NR) | ((BB) << 8): return pack_word_c<NR, BB>(D, lo_M, lo_s, pw_lo, c_hi, c_lo, mc);
         REDASH_RW(16, 2) REDASH_RW(1, 2) REDASH_RW(10, 3) REDASH_RW(6, 3) REDASH_RW(8, 4) REDASH_RW(6, 4)
         REDASH_RW(3, 4) REDASH_RW(6, 5) REDASH_RW(5, 5) REDASH_RW(3, 5) REDASH_RW(2, 5) REDASH_RW(1, 5)
         REDASH_RW(5, 6) REDASH_RW(3, 3) REDASH_RW(4, 7) REDASH_RW(3, 7) REDASH_RW(4, 8) REDASH_RW(2, 8)
 #undef REDASH_RW
         default: {
             uint32_t res = 0;
-            for (uint32_t j = nres; j-- > 0;) {
-                uint32_t p = D;
-                if (j) {
-                    const uint32_t q = div_m(D, mc);
-                    p = D - q * mc.m;
-                    D = q;
-                }
-                res |= sub_mod(field(bw, j, mc), p, mc.m) << (mc.b * j);
+            for (uint32_t j = nres; j-- > 1;) {
+                const uint32_t q = div_m(D, mc);
+                res |= (D - q * mc.m) << (mc.b * j);
+                D = q;
             }
-            return res;
+            return res | D;
         }
     }
+}
+
+// The pad words D (pad_words_top, pad_words_all) as packed residues, in place
+// (m = 2: they are packed already).  The full words' shape is dispatched once.
+template <int NR, int BB>
+__device__ __forceinline__ void pack_full_words(uint32_t (&D)[kMaxW], const ModConst &mc) {
+    static_for<kMaxW - 1>([&](auto p) {
+        if (p > 0 || mc.W == kMaxW)  // five or six words where the fast constants are set
+            D[p] = pack_word_c<NR, BB>(D[p], mc.lo_M_f, mc.lo_s_f, mc.pw_lo_f, mc.fc_hi_f, mc.fc_lo_f, mc);
+    });
+}
+
+__device__ __forceinline__ void pack_pad(uint32_t (&D)[kMaxW], const ModConst &mc) {
+    if (mc.m == 2) return;
+    switch (mc.fast && mc.fd ? mc.g | (mc.b << 8) : 0u) {
+#define REDASH_FULL(NR, BB) \
+    case (NR) | ((BB) << 8): pack_full_words<NR, BB>(D, mc); break;
+        REDASH_FULL(16, 2) REDASH_FULL(10, 3) REDASH_FULL(8, 4) REDASH_FULL(6, 5) REDASH_FULL(5, 6)
+        REDASH_FULL(4, 7) REDASH_FULL(4, 8)
+#undef REDASH_FULL
+        default: {
+            const int off = kMaxW - static_cast<int>(mc.W);
+            static_for<kMaxW - 1>([&](auto p) {
+                if (p >= off) D[p] = pack_word_any(D[p], mc.g, 0, 0, 0, 0, 0, mc);
+            });
+        }
+    }
+    D[kMaxW - 1] = pack_word_any(D[kMaxW - 1], mc.glast, mc.lo_M_l, mc.lo_s_l, mc.pw_lo_l, mc.fc_hi_l, mc.fc_lo_l, mc);
 }
 
 // (x + u) mod m in every field of one packed word (m > 2) at once, with u
@@ -673,6 +691,11 @@ __device__ __forceinline__ uint32_t swar_add(uint32_t x, uint32_t ue, uint32_t u
     const uint32_t ce = ((se + mc.sw_k) >> mc.b) & mc.sw_ones;
     const uint32_t co = ((so + mc.sw_k) >> mc.b) & mc.sw_ones;
     return (se - ce * mc.m) | ((so - co * mc.m) << mc.b);
+}
+
+// (x - u) mod m in every field (m > 2): x + (m - u), km = m in every even field.
+__device__ __forceinline__ uint32_t swar_sub(uint32_t x, uint32_t u, uint32_t km, const ModConst &mc) {
+    return swar_add(x, km - (u & mc.sw_even), km - ((u >> mc.b) & mc.sw_even), mc);
 }
 
 // (x + u) mod m residue by residue for one packed word (any m; m = 2 is XOR).
@@ -728,46 +751,6 @@ __device__ __forceinline__ void hash_fraction(const uint32_t *T, uint32_t x0, ui
     V[5] = h1;
     V[6] = h2;
     V[7] = h3;
-}
-
-// The hash fractions of NG gates that share one input label (folded into
-// x0..x3): gate j uses tweak tau + j and two blocks (a gate whose output
-// modulus is 2 only reads V[j][0..3]).
-template <int NG, bool PAIRED = false, typename Tab, typename Key>
-__device__ __forceinline__ void hash_fraction_n(const Tab &T, const Key &rk, uint32_t x0, uint32_t x1, uint32_t x2,
-                                                uint32_t x3, uint64_t tau, uint32_t gid, uint32_t (&V)[NG][8]) {
-    const uint32_t u0 = x2, u1 = x3, u2 = x2 ^ x0, u3 = x3 ^ x1;
-    uint32_t s[2 * NG][4];
-#pragma unroll
-    for (int j = 0; j < NG; ++j) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint64_t tw = (tau + static_cast<uint64_t>(j)) * 4u + static_cast<uint64_t>(h);
-            s[2 * j + h][0] = u0 ^ static_cast<uint32_t>(tw);
-            s[2 * j + h][1] = u1 ^ static_cast<uint32_t>(tw >> 32);
-            s[2 * j + h][2] = u2;
-            s[2 * j + h][3] = u3 ^ gid;
-        }
-    }
-    aes128_encrypt_n<2 * NG, PAIRED>(T, s, rk);
-    // Matyas-Meyer-Oseas feed-forward of the block input u ^ T.  The inputs
-    // are formed again from x and tau rather than kept through the rounds
-    // (opaque keeps the compiler from reusing the earlier values): six
-    // registers live across the AES instead of up to twelve.
-    const uint32_t y0 = opaque(x0), y1 = opaque(x1), y2 = opaque(x2), y3 = opaque(x3);
-    const uint64_t tau2 = (static_cast<uint64_t>(opaque(static_cast<uint32_t>(tau >> 32))) << 32) |
-                          opaque(static_cast<uint32_t>(tau));
-#pragma unroll
-    for (int j = 0; j < NG; ++j) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint64_t tw = (tau2 + static_cast<uint64_t>(j)) * 4u + static_cast<uint64_t>(h);
-            V[j][4 * h + 0] = s[2 * j + h][0] ^ y2 ^ static_cast<uint32_t>(tw);
-            V[j][4 * h + 1] = s[2 * j + h][1] ^ y3 ^ static_cast<uint32_t>(tw >> 32);
-            V[j][4 * h + 2] = s[2 * j + h][2] ^ y2 ^ y0;
-            V[j][4 * h + 3] = s[2 * j + h][3] ^ y3 ^ y1 ^ gid;
-        }
-    }
 }
 
 // The two-block hashes of NG gates, the AES blocks of all of them round by

@@ -53,7 +53,12 @@ constexpr int kEvalWaves = 6;
 constexpr int kLaneBlock = 1024;
 constexpr int kLaneWaves = 8;
 // The garbler: the same LDS image without the free-operation tables; two
-// workgroups of 512 per CU, four waves per SIMD (up to 128 VGPRs).
+// workgroups of 512 per CU, four waves per SIMD (92 VGPRs).  A gadget is a
+// chain of 1,027 hashes on the 12-prime base, so calls that do not fill the
+// chip split its gates over waves: 1,000 gadgets 6.98 -> 1.53 ms, 50,176
+// 8.1 -> 3.0 ms; larger ones are bound by the vector ALU and the LDS pipe
+// (200,704 gadgets 12.3 -> 10.0 ms, 802,816 42.2 -> 37.0 with shared rounds,
+// truncated pads and rows subtracted a word at a time).
 constexpr int kGarbleBlock = 512;
 constexpr int kGarbleWaves = 4;
 
@@ -538,20 +543,21 @@ __global__ void __launch_bounds__(64) k_offsets(const Plan P, const SeedKey key,
     const ModConst &mc = P.mod[i];
     uint32_t V[8];
     prg_fraction(TT, key.w, 1u, i, V);
-    uint32_t words[kMaxW] = {0, 0, 0, 0, 0, 0};
-    for (uint32_t r = 0; r < mc.lam; ++r) {
-        const uint32_t radix = r ? mc.m : mc.r0;
-        uint32_t dgt = frac_mul_carry(V, radix);
-        if (r == 0) dgt = (mc.r0 == mc.m - 1) ? dgt + 1 : 2 * dgt + 1;
-        const uint32_t w = r / mc.g, pos = r % mc.g;
-#pragma unroll
-        for (int ww = 0; ww < kMaxW; ++ww)
-            if (ww == static_cast<int>(w)) words[ww] |= dgt << (mc.b * pos);
-    }
+    // residue 0, then the digits of a packed word at a time (the g - 1 left of
+    // word 0, g of the next ones, glast of the last)
+    const uint32_t d0 = frac_mul_carry(V, mc.r0);
+    const uint32_t first = (mc.r0 == mc.m - 1) ? d0 + 1 : 2 * d0 + 1;
     for (uint32_t w = 0; w < mc.W; ++w) {
-#pragma unroll
-        for (int ww = 0; ww < kMaxW; ++ww)
-            if (ww == static_cast<int>(w)) offsets[mc.woff + w] = words[ww];
+        const uint32_t nres = w + 1 == mc.W ? mc.glast : mc.g, j0 = w == 0 ? 1u : 0u;
+        uint32_t pw = 1;  // m^(nres - j0); 0 stands for 2^32
+        for (uint32_t j = j0; j < nres; ++j) pw *= mc.m;
+        uint32_t D = nres > j0 ? frac_carry_any(V, pw) : 0u, word = w == 0 ? first : 0u;
+        for (uint32_t j = nres; j-- > j0;) {
+            const uint32_t q = D / mc.m;
+            word |= (D - q * mc.m) << (mc.b * j);
+            D = q;
+        }
+        offsets[mc.woff + w] = word;
     }
 }
 
@@ -570,109 +576,64 @@ __device__ __forceinline__ uint32_t inverse_unit(uint32_t r, const ModConst &mc)
 // The garbler's label access: like the evaluator's, except that a label read
 // from the input tensor (the input zero-labels Z) is taken as Z - (P/2 mod m) R,
 // the ShiftUp of Sec. 3.4 applied as a free constant addition.
+// Right-aligned, as the register labels; its word 0 is at position `off`.
 __device__ __forceinline__ void load_zero_label(const LabelBufs &LB, uint32_t loc, const ModConst &mc,
                                                 const uint32_t *__restrict__ offsets, uint32_t (&L)[kMaxW]) {
-    static_for<kMaxW>([&](auto w) { L[w] = 0; });
+    static_for<kMaxW>([&](auto p) { L[p] = 0; });
     if (loc == kLocZero) return;
-    const uint32_t *p = LB.base(loc, mc);
+    const uint32_t *b = LB.base(loc, mc);
     const uint32_t neg_up = (mc.m - mc.up) % mc.m;
-    static_for<kMaxW>([&](auto w) {
-        if (w < static_cast<int>(mc.W)) {
-            L[w] = LB.get(p, w);
-            if (loc == kLocIn) L[w] = label_axpy(L[w], offsets[mc.woff + w], neg_up, w, mc);
+    const int off = kMaxW - static_cast<int>(mc.W);
+    static_for<kMaxW>([&](auto p) {
+        if (p >= off) {
+            L[p] = LB.get(b, p - off);
+            if (loc == kLocIn) L[p] = label_axpy(L[p], offsets[mc.woff + p - off], neg_up, p - off, mc);
         }
     });
 }
 
-// One garbled row over Z_m: (B - pad) word by word, pad the first lambda_m
-// base-m digits of the hash fraction V (consumed), stored at rp.
-__device__ __forceinline__ void store_row(uint32_t (&V)[8], const uint32_t (&B)[kMaxW], const ModConst &mm,
-                                          uint32_t *rp) {
-    if (mm.m == 2) {
-#pragma unroll
-        for (int w = 0; w < 4; ++w) rp[w] = B[w] ^ bits_word(V, w);
-        return;
-    }
-    uint32_t b[kMaxW];
-    static_for<kMaxW>([&](auto w) { b[w] = B[w]; });
-    if (mm.fast) {
-#pragma unroll 1
-        for (uint32_t w = 0; w + 1 < mm.W; ++w) {
-            const uint32_t D = frac_mul_carry(V, mm.pw_g);
-            rp[w] = row_word_any(D, mm.g, mm.lo_M_f, mm.lo_s_f, mm.pw_lo_f, mm.fc_hi_f, mm.fc_lo_f, next_word(b), mm);
-        }
-        const uint32_t D = frac_mul_carry(V, mm.pw_last);
-        rp[mm.W - 1] = row_word_any(D, mm.glast, mm.lo_M_l, mm.lo_s_l, mm.pw_lo_l, mm.fc_hi_l, mm.fc_lo_l, b[0], mm);
-    } else {
-#pragma unroll 1
-        for (uint32_t w = 0; w < mm.W; ++w) rp[w] = label_sub(next_word(b), pad_word(V, w, mm), w, mm);
-    }
+// A row of W words (4, 5 or 6) from a right-aligned register label.
+__device__ __forceinline__ void store_row(const uint32_t (&row)[kMaxW], uint32_t *rp, uint32_t W) {
+    typedef uint32_t u4 __attribute__((ext_vector_type(4), aligned(4)));
+    u4 v;
+    v.x = row[2];
+    v.y = row[3];
+    v.z = row[4];
+    v.w = row[5];
+    *reinterpret_cast<u4 *>(rp + (W - 4)) = v;
+    if (W > 4) rp[W - 5] = row[1];
+    if (W > 5) rp[0] = row[0];
 }
 
-// Hash fractions of two labels (folded into xa, xb) under the same tweak tau:
-// the four AES blocks run interleaved.
-__device__ __forceinline__ void hash_fraction_two(const PermTE02 &T, const LdsKey &rk, const uint32_t (&xa)[4],
-                                                  const uint32_t (&xb)[4], uint64_t tau, uint32_t gid,
-                                                  uint32_t (&Va)[8], uint32_t (&Vb)[8]) {
-    uint32_t u[2][4], s[4][4], k0[2], k1[2];
-    static_for<2>([&](auto j) {
-        const uint32_t(&x)[4] = j ? xb : xa;
-        u[j][0] = x[2];
-        u[j][1] = x[3];
-        u[j][2] = x[2] ^ x[0];
-        u[j][3] = x[3] ^ x[1];
-    });
-    static_for<2>([&](auto h) {
-        const uint64_t tw = tau * 4u + static_cast<uint64_t>(h);
-        k0[h] = static_cast<uint32_t>(tw);
-        k1[h] = static_cast<uint32_t>(tw >> 32);
-    });
-    static_for<2>([&](auto j) {
-        static_for<2>([&](auto h) {
-            s[2 * j + h][0] = u[j][0] ^ k0[h];
-            s[2 * j + h][1] = u[j][1] ^ k1[h];
-            s[2 * j + h][2] = u[j][2];
-            s[2 * j + h][3] = u[j][3] ^ gid;
-        });
-    });
-    aes128_encrypt_n<4>(T, s, rk);
-    static_for<2>([&](auto h) {
-        Va[4 * h + 0] = s[h][0] ^ u[0][0] ^ k0[h];
-        Va[4 * h + 1] = s[h][1] ^ u[0][1] ^ k1[h];
-        Va[4 * h + 2] = s[h][2] ^ u[0][2];
-        Va[4 * h + 3] = s[h][3] ^ u[0][3] ^ gid;
-        Vb[4 * h + 0] = s[2 + h][0] ^ u[1][0] ^ k0[h];
-        Vb[4 * h + 1] = s[2 + h][1] ^ u[1][1] ^ k1[h];
-        Vb[4 * h + 2] = s[2 + h][2] ^ u[1][2];
-        Vb[4 * h + 3] = s[2 + h][3] ^ u[1][3] ^ gid;
-    });
-}
-
+// XOR-fold of a right-aligned label over the modulus mq.
 __device__ __forceinline__ void fold_label(const uint32_t (&A)[kMaxW], const ModConst &mq, uint32_t (&x)[4]) {
-    x[0] = A[0];
-    x[1] = x[2] = x[3] = 0;
-    static_for<kMaxW - 1>([&](auto w1) {
-        constexpr int w = decltype(w1)::value + 1;
-        if (w < static_cast<int>(mq.W)) x[w & 3] ^= A[w];
-    });
+    static_for<4>([&](auto l) { x[l] = 0; });
+    switch (label_off(mq)) {
+        case 0: fold_regs<0>(A, x); break;
+        case 1: fold_regs<1>(A, x); break;
+        default: fold_regs<2>(A, x); break;
+    }
 }
 
 // Garbler (Sec. 2.3 projection gates with row reduction, the gadget of
-// Sec. 3.4 applied to zero-labels).  One thread per gadget; labels live
-// where the evaluator keeps them (zin read with the ShiftUp, zout, work).
+// Sec. 3.4 applied to zero-labels).  `split` waves share 64 gadgets, one per
+// lane: within a run of gates that share a digit label (distinct destinations)
+// wave j of them takes gates j, j + split, ...; a workgroup barrier between
+// runs publishes the updated labels.  Labels live where the evaluator keeps
+// them (zin read with the ShiftUp, zout, work).
 // Per gate q -> m the q labels of the digit wire are walked by colour:
 // colour c holds the value v_c = (c - c_0) R_q[0]^{-1} mod q, so the label
 // steps by the uniform label R_q[0]^{-1} R_q.  Colour 0 gives
 // B0 = H(A_{v_0}) - (v_0 mod m) R_m; colour c >= 1 gives the row
-// B0 + (v_c mod m) R_m - H(A_{v_c}), two colours per AES batch.  The walk
-// keeps B_c = B0 + (v_c mod m) R_m, starting from B_0 = H(A_{v_0}).
+// B0 + (v_c mod m) R_m - H(A_{v_c}).  The walk keeps B_c = B0 + (v_c mod m) R_m,
+// starting from B_0 = H(A_{v_0}).
 // GIVEN: the input zero-labels are the caller's (zin, read only; zin_w
 // unused), e.g. the output zero-labels of a garbled linear layer; otherwise
 // they are drawn from the PRG into zin_w (== zin).
 template <int BLOCK, bool GIVEN>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kGarbleWaves, kGarbleWaves)))
 k_garble(const Plan P, const SeedKey key, const uint32_t *__restrict__ offsets, const uint32_t *zin,
-         uint32_t *zin_w, uint32_t *zout, uint32_t *__restrict__ tab, uint32_t *work) {
+         uint32_t *zin_w, uint32_t *zout, uint32_t *__restrict__ tab, uint32_t *work, uint32_t split) {
     extern __shared__ uint32_t lds[];
     uint32_t *K = lds + kTableRegionBytes / 4;
     const int tid = threadIdx.x;
@@ -682,14 +643,17 @@ k_garble(const Plan P, const SeedKey key, const uint32_t *__restrict__ offsets, 
     __syncthreads();
     const PermTE02 TT = perm_te02();
     const LdsKey HK{K};
-    const uint64_t a = static_cast<uint64_t>(blockIdx.x) * nthr + tid;
-    if (a >= P.n) return;  // no barrier follows
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(tid) / 64u);
+    const uint32_t part = wave % split;
+    const uint64_t a = (static_cast<uint64_t>(blockIdx.x) * (static_cast<uint32_t>(nthr) / 64u / split) + wave / split) * 64u +
+                       static_cast<uint32_t>(tid) % 64u;
+    const bool live = a < P.n;  // dead lanes still take every barrier
     const uint64_t n = P.n;
     const uint64_t ga = P.a0 + a;
-    const LabelBufs LB{zin, zout, work, n, static_cast<uint32_t>(a) * 4u};
+    const LabelBufs LB{zin, zout, work, n, static_cast<uint32_t>(live ? a : 0) * 4u};
 
     // Input zero-labels Z: digits of rho(2, ga k + i) (Sec. 2.3 label sampling).
-    for (uint32_t i = 0; i < (GIVEN ? 0u : P.k); ++i) {
+    for (uint32_t i = part; i < (GIVEN || !live ? 0u : P.k); i += split) {
         const ModConst mc = P.mod[i];
         uint32_t s[1][4];
         uint32_t V[8];
@@ -705,126 +669,120 @@ k_garble(const Plan P, const SeedKey key, const uint32_t *__restrict__ offsets, 
         uint32_t *dst = zin_w + static_cast<uint64_t>(mc.woff) * n;
         for (uint32_t w = 0; w < mc.W; ++w) LB.put(dst, w, prg_word(V, w, mc));
     }
+    __syncthreads();
 
     const uint64_t tau0 = ga * P.G;
     uint64_t toff = 0;
+    uint32_t run = 0;  // the first gate of the run of gates that share g's digit
     for (uint32_t g = 0; g < P.G; ++g) {
         const uint32_t d = P.gate[g];
         const ModConst mq = P.mod[gate_src(d)];
         const ModConst mm = P.mod[gate_dst(d)];
+        if (g > 0 && gate_src(d) != gate_src(P.gate[g - 1])) {
+            // the labels that the run before wrote are read from here on
+            __syncthreads();
+            run = g;
+        }
+        if ((g - run) % split != part || !live) {
+            toff += n * (mq.m - 1) * mm.W;
+            continue;
+        }
         const uint32_t q = mq.m, m = mm.m;
+        // (labels over the output modulus are right-aligned, as the pads)
+        const int off = kMaxW - static_cast<int>(mm.W);
         uint32_t Rq[kMaxW], Rm[kMaxW];
+        const int qoff = kMaxW - static_cast<int>(mq.W);
         static_for<kMaxW>([&](auto w) {
-            Rq[w] = w < static_cast<int>(mq.W) ? offsets[mq.woff + w] : 0u;
-            Rm[w] = w < static_cast<int>(mm.W) ? offsets[mm.woff + w] : 0u;
+            Rq[w] = w >= qoff ? offsets[mq.woff + w - qoff] : 0u;
+            Rm[w] = w >= off ? offsets[mm.woff + w - off] : 0u;
         });
-        uint32_t A[kMaxW], T[kMaxW];
+        uint32_t A[kMaxW];
         load_zero_label(LB, gate_dsrc(d), mq, offsets, A);
-        load_zero_label(LB, gate_tsrc(d), mm, offsets, T);
-        const uint32_t rinv = inverse_unit(Rq[0] & mq.mask, mq);
+        const uint32_t rinv = inverse_unit(offsets[mq.woff] & mq.mask, mq);
         // v: the value of colour 0; A <- A0 + v R_q
-        uint32_t v = mul_mod((q - (A[0] & mq.mask)) % q, rinv, mq);
+        const uint32_t a00 = (qoff == 0 ? A[0] : qoff == 1 ? A[1] : A[2]) & mq.mask;
+        uint32_t v = mul_mod((q - a00) % q, rinv, mq);
         static_for<kMaxW>([&](auto w) {
-            if (w < static_cast<int>(mq.W)) A[w] = label_axpy(A[w], Rq[w], v, w, mq);
+            if (w >= qoff) A[w] = label_axpy(A[w], Rq[w], v, w - qoff, mq);
         });
         // uniform steps: the input label by rinv R_q, the output label by
-        // (rinv mod m) R_m, or ((rinv - q) mod m) R_m when v wraps past q
-        // (split into even and odd fields for swar_add; m = 2 steps by XOR)
+        // (rinv mod m) R_m, or ((rinv - q) mod m) R_m when v wraps past q (in
+        // vector registers: there are too many for the scalar ones)
         const uint32_t s1 = rinv % m, s2 = (rinv % m + m - q % m) % m;
-        uint32_t Rse[kMaxW], Rso[kMaxW], U1e[kMaxW], U1o[kMaxW], U2e[kMaxW], U2o[kMaxW];
+        uint32_t Rse[kMaxW], Rso[kMaxW], U1[kMaxW], U2[kMaxW];
         static_for<kMaxW>([&](auto w) {
-            const uint32_t rs = w < static_cast<int>(mq.W) ? label_axpy(0u, Rq[w], rinv, w, mq) : 0u;
-            const uint32_t u1 = w < static_cast<int>(mm.W) ? label_axpy(0u, Rm[w], s1, w, mm) : 0u;
-            const uint32_t u2 = w < static_cast<int>(mm.W) ? label_axpy(0u, Rm[w], s2, w, mm) : 0u;
-            Rse[w] = q == 2 ? rs : rs & mq.sw_even;
-            Rso[w] = (rs >> mq.b) & mq.sw_even;
-            U1e[w] = m == 2 ? u1 : u1 & mm.sw_even;
-            U1o[w] = (u1 >> mm.b) & mm.sw_even;
-            U2e[w] = m == 2 ? u2 : u2 & mm.sw_even;
-            U2o[w] = (u2 >> mm.b) & mm.sw_even;
+            const uint32_t rs = w >= qoff ? label_axpy(0u, Rq[w], rinv, w - qoff, mq) : 0u;
+            Rse[w] = opaque(q == 2 ? rs : rs & mq.sw_even);
+            Rso[w] = opaque((rs >> mq.b) & mq.sw_even);
+            U1[w] = opaque(w >= off ? label_axpy(0u, Rm[w], s1, w - off, mm) : 0u);
+            U2[w] = opaque(w >= off ? label_axpy(0u, Rm[w], s2, w - off, mm) : 0u);
         });
-        const uint64_t tau = tau0 + g;
-
-        // colour 0: the pad H(A_v0) starts the walk B_c = B0 + (v_c mod m) R_m,
-        // with B0 = H(A_v0) - (v0 mod m) R_m (row reduction: no row stored)
         uint32_t B[kMaxW];
-        {
-            uint32_t x[4], V0[1][8];
-            fold_label(A, mq, x);
-            hash_fraction_n<1>(TT, HK, x[0], x[1], x[2], x[3], tau, P.gid, V0);
-            static_for<kMaxW>([&](auto w) { B[w] = 0; });
+        static_for<kMaxW>([&](auto w) { B[w] = 0; });
+        uint32_t *row_at = tab + toff + a * (q - 1) * mm.W;
 #pragma unroll 1
-            for (uint32_t w = 0; w < mm.W; ++w) {
-                const uint32_t pw = pad_word(V0[0], w, mm);
-                static_for<kMaxW>([&](auto ww) {
-                    if (ww == static_cast<int>(w)) B[ww] = pw;
+        for (uint32_t c = 0; c < q; ++c) {
+            // (the moduli's constants are loaded where they are used, not held in
+            // scalar registers through the hash: two sets do not fit)
+            uint32_t dc = d;
+            asm volatile("" : "+s"(dc));
+            if (c != 0) {
+                const ModConst mq = P.mod[gate_src(dc)], mm = P.mod[gate_dst(dc)];
+                static_for<kMaxW>([&](auto w) {
+                    if (w >= kMaxW - static_cast<int>(mq.W))
+                        A[w] = q == 2 ? A[w] ^ Rse[w] : swar_add(A[w], Rse[w], Rso[w], mq);
+                });
+                const uint32_t vn = v + rinv;
+                const bool wrap = vn >= q;
+                v = wrap ? vn - q : vn;
+                static_for<kMaxW>([&](auto w) {
+                    if (w >= off) {
+                        const uint32_t u = wrap ? U2[w] : U1[w];
+                        B[w] = m == 2 ? B[w] ^ u : swar_add(B[w], u & mm.sw_even, (u >> mm.b) & mm.sw_even, mm);
+                    }
                 });
             }
-        }
-        // The free operation on the destination zero-label, as the evaluator
-        // applies it to labels (E replaced by B0).
-        {
-            const uint32_t coeff = gate_coeff(d);
-            const uint32_t negv = (m - v % m) % m;
-            uint32_t *dst = LB.dest(gate_tdst(d), mm);
-            static_for<kMaxW>([&](auto w) {
-                if (w < static_cast<int>(mm.W)) {
-                    const uint32_t b0 = label_axpy(B[w], Rm[w], negv, w, mm);
-                    LB.put(dst, w,
-                           gate_kind(d) == 0 ? label_scaled_sub(T[w], b0, coeff, w, mm)
-                                             : label_axpy(T[w], b0, coeff, w, mm));
-                }
-            });
-        }
-        // colours 1..q-1, two per AES batch
-        uint32_t *gate_rows = tab + toff + a * (q - 1) * mm.W;
-        auto step = [&](uint32_t(&Ax)[kMaxW], uint32_t(&Bx)[kMaxW], uint32_t &vx) {
-            static_for<kMaxW>([&](auto w) {
-                if (w < static_cast<int>(mq.W)) Ax[w] = q == 2 ? Ax[w] ^ Rse[w] : swar_add(Ax[w], Rse[w], Rso[w], mq);
-            });
-            const uint32_t vn = vx + rinv;
-            const bool wrap = vn >= q;
-            vx = wrap ? vn - q : vn;
-            static_for<kMaxW>([&](auto w) {
-                if (w < static_cast<int>(mm.W))
-                    Bx[w] = m == 2 ? Bx[w] ^ (wrap ? U2e[w] : U1e[w])
-                                   : swar_add(Bx[w], wrap ? U2e[w] : U1e[w], wrap ? U2o[w] : U1o[w], mm);
-            });
-        };
-#pragma unroll 1
-        for (uint32_t c = 1; c < q; c += 2) {
-            step(A, B, v);
-            if (c + 1 < q) {
-                uint32_t A2[kMaxW], B2[kMaxW];
-                uint32_t v2 = v;
-                static_for<kMaxW>([&](auto w) {
-                    A2[w] = A[w];
-                    B2[w] = B[w];
-                });
-                step(A2, B2, v2);
-                uint32_t xa[4], xb[4], Va[8], Vb[8];
-                fold_label(A, mq, xa);
-                fold_label(A2, mq, xb);
-                hash_fraction_two(TT, HK, xa, xb, tau, P.gid, Va, Vb);
-                store_row(Va, B, mm, gate_rows + (c - 1) * mm.W);
-                store_row(Vb, B2, mm, gate_rows + c * mm.W);
-                static_for<kMaxW>([&](auto w) {
-                    A[w] = A2[w];
-                    B[w] = B2[w];
-                });
-                v = v2;
+            // the packed pad of the label A under the gate's tweak
+            uint32_t x[4], V[1][8], D[kMaxW];
+            fold_label(A, P.mod[gate_src(dc)], x);
+            auto tweak = [&] { return opaque64(tau0 + g); };
+            hash_pairs<1>(TT, HK, x, tweak, P.gid, P.mod[gate_dst(dc)].pad_amb == 0, V);
+            asm volatile("" : "+s"(dc));
+            const ModConst mm = P.mod[gate_dst(dc)];
+            gate_pad(TT, K, P.gid, mm, V[0], D, [&](uint32_t(&f)[4]) { fold_label(A, P.mod[gate_src(dc)], f); }, tweak);
+            pack_pad(D, mm);
+            if (c != 0) {
+                // colours 1..q-1: the row B_c - H(A_{v_c})
+                static_for<kMaxW>([&](auto p) { D[p] = m == 2 ? B[p] ^ D[p] : swar_sub(B[p], D[p], mm.sw_ones * m, mm); });
+                store_row(D, row_at, mm.W);
+                row_at += mm.W;
             } else {
-                uint32_t x[4], V1[1][8];
-                fold_label(A, mq, x);
-                hash_fraction_n<1>(TT, HK, x[0], x[1], x[2], x[3], tau, P.gid, V1);
-                store_row(V1[0], B, mm, gate_rows + (c - 1) * mm.W);
+                // colour 0: the pad H(A_v0) starts the walk B_c = B0 + (v_c mod m) R_m,
+                // with B0 = H(A_v0) - (v0 mod m) R_m (row reduction: no row stored);
+                // the free operation on the destination zero-label is the
+                // evaluator's on labels, E replaced by B0
+                uint32_t T[kMaxW];
+                load_zero_label(LB, gate_tsrc(d), mm, offsets, T);
+                const uint32_t coeff = gate_coeff(d);
+                const uint32_t negv = (m - v % m) % m;
+                uint32_t *dst = LB.dest(gate_tdst(d), mm);
+                static_for<kMaxW>([&](auto p) {
+                    B[p] = D[p];
+                    if (p >= off) {
+                        const uint32_t w = p - off;
+                        const uint32_t b0 = label_axpy(D[p], offsets[mm.woff + w], negv, w, mm);
+                        LB.put(dst, w, gate_kind(d) == 0 ? label_scaled_sub(T[p], b0, coeff, w, mm)
+                                                         : label_axpy(T[p], b0, coeff, w, mm));
+                    }
+                });
             }
         }
         toff += n * (q - 1) * mm.W;
     }
     // Output zero-labels: the working labels plus (P/(2s) mod m) R, the
     // ShiftDown of Sec. 3.4.
-    for (uint32_t i = 0; i < P.k; ++i) {
+    __syncthreads();
+    for (uint32_t i = live ? part : P.k; i < P.k; i += split) {
         const ModConst mc = P.mod[i];
         uint32_t *p = zout + static_cast<uint64_t>(mc.woff) * n;
         for (uint32_t w = 0; w < mc.W; ++w)
@@ -1195,10 +1153,16 @@ int garble_scale(const redash_params *p, uint32_t *d_offsets, const uint32_t *d_
     const uint32_t lds = kEvalTableBase;  // the AES image and the round keys
     if (lds > max_lds) return REDASH_E_HIP;
     if ((rc = allow_lds(reinterpret_cast<const void *>(&k_garble<kGarbleBlock, GIVEN>), lds))) return rc;
-    int block = 0;
-    if ((rc = block_for(P.n, kGarbleBlock, &block))) return rc;
-    hipLaunchKernelGGL((k_garble<kGarbleBlock, GIVEN>), dim3(grid_for(P.n, block)), dim3(block), lds, stream, P, key,
-                       d_offsets, d_in_zero, d_in_zero_w, d_out_zero, d_tables, d_work);
+    // waves per 64 gadgets: as many as one round of two workgroups per CU
+    // holds (a gadget's gates in turn are a long chain), at most 8
+    DeviceInfo dev;
+    if ((rc = device_info(&dev))) return rc;
+    uint32_t split = 8;
+    while (split > 1 && P.n > 2ull * static_cast<uint64_t>(dev.cus) * (kGarbleBlock / split)) split /= 2;
+    int per = 0;  // gadgets per workgroup
+    if ((rc = block_for(P.n, kGarbleBlock / static_cast<int>(split), &per))) return rc;
+    hipLaunchKernelGGL((k_garble<kGarbleBlock, GIVEN>), dim3(grid_for(P.n, per)), dim3(per * static_cast<int>(split)), lds,
+                       stream, P, key, d_offsets, d_in_zero, d_in_zero_w, d_out_zero, d_tables, d_work, split);
     return launched();
 }
 

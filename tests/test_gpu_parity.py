@@ -595,6 +595,18 @@ def test_one_gadget_per_lane_past_the_round_and_rest_on_varied_bases(name, modul
     _check_full(w, 2048, 2048, 2048, 8)
 
 
+# The garbler gives 64 gadgets 8, 4, 2 or 1 waves, as many as one round of two
+# workgroups of 8 waves per CU holds: the last call of each size and one past it.
+@pytest.mark.parametrize("per,extra", [(64, 0), (64, 1), (128, 0), (128, 1), (256, 0), (256, 1)])
+def test_garbler_launch_thresholds(per, extra):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    moduli = (2, 3, 5, 7, 11, 13)
+    P = rns.cardinality(moduli)
+    w = WL.Workload(f"garble-{per}-{extra}", moduli, (1, 4), 2 * cus * per + extra, 110 + per + extra, "uniform",
+                    -(P // 2), P - P // 2)
+    _check_full(w, 1024, 1024, 2048, 16)
+
+
 RANDOM_LANE_BASES = [c[:3] for c in _random_bases(4, 7207)]
 
 
