@@ -75,7 +75,8 @@ struct LinPlan {
     uint32_t rows, cols, nimg;    // output rows, columns, images (dense: 1, batch, 1)
     uint32_t sN, sC, sY, sX;      // input activation index = img sN + c sC + y sY + x sX
     uint32_t oN, oO, oY, oX;      // output activation index, likewise
-    uint32_t hp, wp, cp;          // plane rows and columns (padded) and channels (ncc ck)
+    uint32_t hp, wp, cp;          // plane rows and columns (padded) and channel bytes per position
+                                  // (ncc ck; folded: the layer's own c_in)
     uint32_t xt, xtiles;          // output positions per tile, tiles per row
     uint32_t ck, kc, taps, ncc;   // channel chunk, K bytes per chunk (64-padded), kh kw, chunks
     uint32_t lg_ck;
@@ -84,13 +85,14 @@ struct LinPlan {
     uint32_t astride;             // LDS bytes per staged weight row
     uint32_t ostride;             // words per output-channel row of the merged output words
     uint32_t xw, xstride;         // staged input columns of a tile; LDS bytes per staged column
+    uint32_t gstep, lstep;        // plane columns between staged ones; staged columns between outputs
+    uint32_t xlast;               // the last plane column that is staged
     uint32_t wpair;               // staging: the two columns of an 8-lane write group lie wpair apart
     uint32_t halo;                // LDS bytes of one residue's staged input (kh xw xstride)
     uint32_t lds_a, lds_b, lds_o, lds_bytes;
     uint32_t npairs;
     uint32_t word_split;          // k_linear_gemm: one workgroup per packed word (else per modulus)
     uint32_t fold_c;              // column fold (see the plan): the layer's own c_in, else 0
-    uint32_t fold_magic;          // floor(c / fold_c) = (c fold_magic) >> 16 for every c < 64
     uint32_t flat, tile_rows;     // k_linear_gemm over the flattened plane (see the plan); rows of tiles
     uint64_t n_in, n_out;         // activations
     uint64_t plane_bytes;         // nimg hp wp cp
@@ -179,21 +181,19 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     }
     L->taps = static_cast<uint32_t>(taps);
     // Column fold: with few input channels the kw columns of a kernel row
-    // become kw c_in channels of a kh x 1 kernel (plane byte (y, x, dx c_in +
-    // c) holds input (y, x + dx, c)), so that a K slice carries kw c_in
-    // weights instead of c_in and up to 16 - c_in zeros (the 7x7 stride-2
-    // stem over 3 channels: 4 K steps of 64 instead of 13), where the staged
-    // halo of a 16-position tile still fits (kh (15 stride + 1) 16-byte
-    // pieces per channel chunk of 16, 32 or 64).  From here on c_in, kw and
-    // taps are those of the folded layer.
+    // become kw c_in channels of a kh x 1 kernel, so that a K slice carries
+    // kw c_in weights instead of c_in and up to 16 - c_in zeros (the 7x7
+    // stride-2 stem over 3 channels: 4 K steps of 64 instead of 13).  The
+    // planes stay unfolded, c_in bytes per position: the kw c_in bytes of a
+    // window are consecutive there, and the staging loads them from the byte
+    // where the window begins (the bytes after it meet zero weights), one
+    // staged column per output column.  Where the staged halo of a 16-position
+    // tile fits (16 kh 16-byte pieces per 16 of the chunk's 16, 32 or 64
+    // channels).  From here on c_in, kw and taps are those of the folded layer.
     L->fold_c = 0;
-    L->fold_magic = 0;
     const uint32_t cf = p->kw * p->c_in, ckf = cf <= 16 ? 16u : cf <= 32 ? 32u : 64u;
-    if (!dense && p->kw > 1 && p->c_in < 16 && cf <= 64 &&
-        p->kh * (15 * p->stride + 1) * (ckf / 16) <= 2 * kLinBlock) {
+    if (!dense && p->kw > 1 && p->c_in < 16 && cf <= 64 && p->kh * 16 * (ckf / 16) <= 2 * kLinBlock) {
         L->fold_c = p->c_in;
-        // ceil(2^16 / c_in): as for the taps below, exact for every c < 64
-        L->fold_magic = ((1u << 16) + p->c_in - 1) / p->c_in;
         L->c_in = p->kw * p->c_in;
         L->kw = 1;
         L->taps = p->kh;
@@ -206,10 +206,12 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     L->lg_ck = ck == 64 ? 6 : ck == 32 ? 5 : 4;
     L->kc = round_up(L->taps * ck, 64);
     L->ncc = (L->c_in + ck - 1) / ck;
-    L->cp = L->ncc * ck;
+    L->cp = L->fold_c ? L->fold_c : L->ncc * ck;
     L->hp = L->in_rows + 2 * p->pad;
-    // folded: plane column x serves output column x / stride
-    L->wp = L->fold_c ? (L->cols - 1) * p->stride + 1 : L->in_cols + 2 * p->pad;
+    L->wp = L->in_cols + 2 * p->pad;
+    L->gstep = L->fold_c ? p->stride : 1;
+    L->lstep = L->fold_c ? 1 : p->stride;
+    L->xlast = L->fold_c ? (L->cols - 1) * p->stride : L->wp - 1;
     // M = ceil(2^16 / kw) <= 2^16: with e = M kw - 2^16 < kw, (t M) >> 16 =
     // floor(t/kw + t e / (kw 2^16)), and t e / 2^16 < 64 kw / 2^16 < 1 keeps
     // the error below 1/kw for every tap t < 64 and kw <= 64 (t M < 2^22: a
@@ -231,10 +233,11 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     // a write group take two columns wpair apart so that their 4 chunks each
     // fall in distinct bank groups (xstride / 16 = 6: 2 apart; 5: 4 apart).
     if (ck == 64) {
-        L->xstride = (p->stride % 2 == 1) ? 96 : 80;
+        L->xstride = (L->lstep % 2 == 1) ? 96 : 80;
         L->wpair = L->xstride == 96 ? 2 : 4;
     } else {
-        L->xstride = ck == 16 ? 16 : ck + 16;
+        // (folded, 32 channels: the two chunks of 16 columns fill 512 bytes)
+        L->xstride = ck == 16 ? 16 : L->fold_c ? ck : ck + 16;
         L->wpair = 1;
     }
     // tile width: 32 or 16 positions, no wider than the row needs (64 would
@@ -242,13 +245,13 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     // 16-byte pieces per residue (two per thread)
     L->xt = 32;
     while (L->xt > 16 && L->xt / 2 >= L->cols) L->xt /= 2;
-    auto pieces = [&](uint32_t xt) { return L->kh * ((xt - 1) * p->stride + L->kw) * (ck / 16); };
+    auto pieces = [&](uint32_t xt) { return L->kh * ((xt - 1) * L->lstep + L->kw) * (ck / 16); };
     if (L->xt == 32 && pieces(32) > 2 * kLinBlock) L->xt = 16;
     // a 3x3 kernel over several 64-channel chunks keeps the next chunk's
     // weights in registers, which only the 16-position tile has room for
     if (L->ncc > 1 && ck == 64 && p->kh == 3 && p->kw == 3) L->xt = 16;
     if (pieces(L->xt) > 2 * kLinBlock) return REDASH_E_PARAM;
-    L->xw = (L->xt - 1) * p->stride + L->kw;
+    L->xw = (L->xt - 1) * L->lstep + L->kw;
     L->halo = L->kh * L->xw * L->xstride;
     L->tile_rows = L->rows;
     // Flattened tiles for narrow rows (3x3, stride 1, several chunks, at
@@ -276,6 +279,8 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     if (L->lds_bytes > kLinMaxLds) return REDASH_E_PARAM;
     L->xtiles = L->flat ? (L->rows * L->wp + 15) / 16 : (L->cols + L->xt - 1) / L->xt;
     L->plane_bytes = static_cast<uint64_t>(L->nimg) * L->hp * L->wp * L->cp;
+    // folded: a window's last piece may be read past the last position
+    if (L->fold_c) L->plane_bytes = (L->plane_bytes + 64 + 63) / 64 * 64;
     if (L->plane_bytes >= (1ull << 32)) return REDASH_E_PARAM;  // 32-bit offsets within a plane
 
     uint32_t woff = 0, pl_off = 0, np = 0;
@@ -416,9 +421,19 @@ __device__ __forceinline__ uint32_t load_word(const uint32_t *base, uint32_t off
 
 typedef int32_t v4i __attribute__((ext_vector_type(4)));
 
+// (from any byte: the pieces of a folded layer begin where their window does)
 __device__ __forceinline__ v4i load16(const uint8_t *base, uint32_t off) {
+    typedef int32_t v4i_any __attribute__((ext_vector_type(4), aligned(1)));
     asm("" : "+v"(off));
-    return *reinterpret_cast<const v4i *>(base + off);
+    return *reinterpret_cast<const v4i_any *>(base + off);
+}
+
+// Byte of plane h (of those of its packed word) for the word wd.
+__device__ __forceinline__ uint32_t plane_byte(uint32_t wd, const LinMod &M, uint32_t h) {
+    if (M.lgf == 0) return __builtin_amdgcn_ubfe(wd, M.b * h, M.b);     // one residue
+    if (M.bp == M.b) return __builtin_amdgcn_ubfe(wd, 8 * h, 8);        // f adjacent fields, as in the word
+    // b = 3: residues 2h and 2h + 1 into 4-bit fields
+    return __builtin_amdgcn_ubfe(wd, 6 * h, 3) | (__builtin_amdgcn_ubfe(wd, 6 * h + 3, 3) << 4);
 }
 
 // A workgroup takes 64 padded positions and one 64-channel chunk of a packed
@@ -461,36 +476,7 @@ __global__ void __launch_bounds__(256) k_linear_unpack(const LinPlan L, const ui
         inside = y >= 0 && y < static_cast<int32_t>(L.in_rows) && x >= 0 && x < static_cast<int32_t>(L.in_cols);
         return inside ? (img * L.sN + static_cast<uint32_t>(y) * L.sY + static_cast<uint32_t>(x) * L.sX) * 4u : 0u;
     };
-    if (L.fold_c) {
-        // folded layer: channel c = dx c_in' + c' of plane column xp is input
-        // channel c' at padded column xp + dx; outside the input the word is
-        // 0, whose fields are the residues of the padding value 0
-        const uint32_t p = tid % 64, c16 = tid / 64, pp = pp0 + p;
-        if (pp < npos && c16 < ngrp) {
-            const uint32_t xp = pp % L.wp, t = pp / L.wp;
-            const int32_t y = static_cast<int32_t>(t % L.hp) - static_cast<int32_t>(L.pad);
-            const uint32_t img = t / L.hp;
-            const uint32_t *src = in + (static_cast<uint64_t>(M.woff) + w) * L.n_in;
-            v4i q4[4];
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint32_t ch = cbase + 16 * c16 + static_cast<uint32_t>(4 * d + k);
-                    const uint32_t dx = __umul24(ch, L.fold_magic) >> 16, c = ch - dx * L.fold_c;
-                    const int32_t x = static_cast<int32_t>(xp + dx) - static_cast<int32_t>(L.pad);
-                    const bool ok = ch < L.c_in && y >= 0 && y < static_cast<int32_t>(L.in_rows) && x >= 0 &&
-                                    x < static_cast<int32_t>(L.in_cols);
-                    const uint32_t a =
-                        ok ? (img * L.sN + static_cast<uint32_t>(y) * L.sY + static_cast<uint32_t>(x) * L.sX + c * L.sC) * 4u
-                           : 0u;
-                    const uint32_t v = load_word(src, a);
-                    q4[d][k] = static_cast<int32_t>(ok ? v : 0u);
-                }
-#pragma unroll
-            for (int d = 0; d < 4; ++d) *reinterpret_cast<v4i *>(&T[p * 68 + 16 * c16 + 4 * d]) = q4[d];
-        }
-    } else {
+    {
         const uint32_t p = tid % 64, c16 = tid / 64, pp = pp0 + p;
         if (pp < npos && c16 < ngrp) {
             bool inside = false;
@@ -519,7 +505,6 @@ __global__ void __launch_bounds__(256) k_linear_unpack(const LinPlan L, const ui
     if (pp >= npos || c16 >= ngrp) return;  // no barrier follows
     bool inside = false;
     (void)at(pp, inside);
-    inside = inside || L.fold_c;  // folded: padding was read as 0 words
     const uint32_t c0 = cbase + 16 * c16;
     uint32_t wd[16];
 #pragma unroll
@@ -539,20 +524,59 @@ __global__ void __launch_bounds__(256) k_linear_unpack(const LinPlan L, const ui
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t q = static_cast<uint32_t>(4 * d + k);
-                uint32_t x;
-                if (M.lgf == 0) {
-                    x = __builtin_amdgcn_ubfe(wd[q], M.b * h, M.b);  // one residue
-                } else if (M.bp == M.b) {
-                    x = __builtin_amdgcn_ubfe(wd[q], 8 * h, 8);  // f adjacent fields, as in the word
-                } else {
-                    // b = 3: residues 2h and 2h + 1 into 4-bit fields
-                    x = __builtin_amdgcn_ubfe(wd[q], 6 * h, 3) | (__builtin_amdgcn_ubfe(wd[q], 6 * h + 3, 3) << 4);
-                }
+                const uint32_t x = plane_byte(wd[q], M, h);
                 y |= (q < nlive ? x : 0u) << (8 * k);
             }
             v[d] = static_cast<int32_t>(y ^ flip);
         }
         *reinterpret_cast<v4i *>(dst + static_cast<uint64_t>(h) * L.plane_bytes) = v;
+    }
+}
+
+// The planes of a folded layer (few channels): c_in bytes per padded position,
+// without gaps.  A thread writes four consecutive bytes of every residue of a
+// packed word.  (The folded planes that this replaces held every window on its
+// own, 7.7 times the bytes for the 7x7 stem: 0.222 ms of unpacking.)
+__global__ void __launch_bounds__(256) k_linear_unpack_rows(const LinPlan L, const uint32_t *__restrict__ in,
+                                                            uint8_t *__restrict__ planes) {
+    const uint32_t pair = blockIdx.y;
+    const uint32_t i = L.pair_mod[pair], w = L.pair_word[pair];
+    const LinMod M = L.mod[i];
+    const uint32_t g = (w + 1 == M.W) ? M.glast : M.g;
+    const uint32_t flip = M.m > 128 ? 0x80808080u : 0u;
+    const uint32_t total = L.nimg * L.hp * L.wp * L.cp;  // below 2^32 (plane_bytes is)
+    const uint32_t b0 = (blockIdx.x * 256 + threadIdx.x) * 4;
+    if (b0 >= total) return;
+    const uint32_t *src = in + (static_cast<uint64_t>(M.woff) + w) * L.n_in;
+    uint32_t wd[4];
+    uint32_t pos = b0 / L.cp, c = b0 - pos * L.cp;
+    uint32_t xp = pos % L.wp, t = pos / L.wp;
+    uint32_t yp = t % L.hp, img = t / L.hp;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int32_t y = static_cast<int32_t>(yp) - static_cast<int32_t>(L.pad);
+        const int32_t x = static_cast<int32_t>(xp) - static_cast<int32_t>(L.pad);
+        const bool inside = img < L.nimg && y >= 0 && y < static_cast<int32_t>(L.in_rows) && x >= 0 &&
+                            x < static_cast<int32_t>(L.in_cols);
+        const uint32_t at =
+            img * L.sN + c * L.sC + static_cast<uint32_t>(y) * L.sY + static_cast<uint32_t>(x) * L.sX;
+        wd[k] = inside ? src[at] : 0u;
+        // the next byte: channel, column, row, image
+        if (++c == L.cp) {
+            c = 0;
+            if (++xp == L.wp) {
+                xp = 0;
+                if (++yp == L.hp) yp = 0, ++img;
+            }
+        }
+    }
+    uint8_t *dst = planes + static_cast<uint64_t>(M.pl_off + w * M.ppw) * L.plane_bytes + b0;
+    const uint32_t nplanes = (g + (1u << M.lgf) - 1) >> M.lgf;
+    for (uint32_t h = 0; h < nplanes; ++h) {
+        uint32_t y = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) y |= plane_byte(wd[k], M, h) << (8 * k);
+        *reinterpret_cast<uint32_t *>(dst + static_cast<uint64_t>(h) * L.plane_bytes) = y ^ flip;
     }
 }
 
@@ -970,8 +994,8 @@ k_linear_gemm_w(const LinPlan L, const uint8_t *__restrict__ planes, const uint8
         uint32_t xin = (ee / c16n) % L.xw;
         const uint32_t grp = 2 * L.wpair, gb = xin - xin % grp;
         if (gb + grp <= L.xw) xin = gb + (xin - gb) / 2 + ((xin - gb) % 2) * L.wpair;
-        uint32_t xp = x0 * L.stride + xin;
-        xp = xp < L.wp ? xp : L.wp - 1;
+        uint32_t xp = x0 * L.stride + xin * L.gstep;
+        xp = xp < L.xlast ? xp : L.xlast;
         poff[s] = ((img * L.hp + row * L.stride + dy) * L.wp + xp) * L.cp + 16 * c16;
         const uint32_t lo = e < pieces ? dy * rowb + xin * L.xstride + 16 * c16 : 0xffffu;
         loff2[s / 2] |= lo << (16 * (s % 2));
@@ -979,7 +1003,7 @@ k_linear_gemm_w(const LinPlan L, const uint8_t *__restrict__ planes, const uint8
     auto loff = [&](int s) -> uint32_t { return (loff2[s / 2] >> (16 * (s % 2))) & 0xffffu; };
     uint32_t colb[NCB];
 #pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) colb[cb] = (cb * 16 + lane % 16) * L.stride * L.xstride;
+    for (int cb = 0; cb < NCB; ++cb) colb[cb] = (cb * 16 + lane % 16) * L.lstep * L.xstride;
 
     // residue (w, j) (field j of packed word w) is in plane pn(w, j) of the
     // modulus; the halo of the next residue is staged after the operations
@@ -1230,8 +1254,12 @@ int launch_linear(const LinPlan &L, const uint32_t *in, const uint8_t *prep, con
     if (L.lds_bytes > static_cast<uint32_t>(v)) return REDASH_E_HIP;
     const uint64_t npos = static_cast<uint64_t>(L.nimg) * L.hp * L.wp;
     if (npos >= (1ull << 32)) return REDASH_E_PARAM;
-    hipLaunchKernelGGL(k_linear_unpack, dim3(static_cast<uint32_t>((npos + 63) / 64), L.npairs, (L.cp + 63) / 64),
-                       dim3(256), 0, stream, L, in, work);
+    if (L.fold_c)
+        hipLaunchKernelGGL(k_linear_unpack_rows, dim3(static_cast<uint32_t>((npos * L.cp + 1023) / 1024), L.npairs),
+                           dim3(256), 0, stream, L, in, work);
+    else
+        hipLaunchKernelGGL(k_linear_unpack, dim3(static_cast<uint32_t>((npos + 63) / 64), L.npairs, (L.cp + 63) / 64),
+                           dim3(256), 0, stream, L, in, work);
     if (lin_launched()) return REDASH_E_HIP;
     if (L.xt == 32) return launch_gemm_k<2, GARBLE>(L, work, prep, bias, offsets, out, stream);
     return launch_gemm_k<1, GARBLE>(L, work, prep, bias, offsets, out, stream);
