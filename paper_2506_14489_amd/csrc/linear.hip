@@ -247,6 +247,10 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     while (L->xt > 16 && L->xt / 2 >= L->cols) L->xt /= 2;
     auto pieces = [&](uint32_t xt) { return L->kh * ((xt - 1) * L->lstep + L->kw) * (ck / 16); };
     if (L->xt == 32 && pieces(32) > 2 * kLinBlock) L->xt = 16;
+    // a folded layer's few K steps leave a wave waiting for its staging and
+    // epilogue: 16-position tiles (122 VGPRs, 33 KB of LDS) run four waves per
+    // SIMD instead of two (7x7 stem 0.298 -> 0.224 ms)
+    if (L->fold_c) L->xt = 16;
     // a 3x3 kernel over several 64-channel chunks keeps the next chunk's
     // weights in registers, which only the 16-position tile has room for
     if (L->ncc > 1 && ck == 64 && p->kh == 3 && p->kw == 3) L->xt = 16;
@@ -594,11 +598,14 @@ __device__ __forceinline__ v4i plane_field(const v4i &v, const LinMod &M, uint32
 // ---------------------------------------------------------------------------
 // The contraction.
 // ---------------------------------------------------------------------------
+// (At least two waves per SIMD; where the registers and the LDS allow three or
+// four, as without K33 on 16-position tiles, they run: 1x1 256 -> 512 stride 2
+// at 14x14 0.121 -> 0.094 ms.)
 // K33 (> 0): a 3x3 kernel with 64-channel chunks (taps = K steps, kc = 576)
 // and K33 bytes per staged column, the K loop unrolled with every fragment
 // offset known but the row stride; 0: any kernel.
 template <int NCB, bool GARBLE, int K33>
-__global__ void __launch_bounds__(kLinBlock) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ void __launch_bounds__(kLinBlock) __attribute__((amdgpu_waves_per_eu(2)))
 k_linear_gemm(const LinPlan L, const uint8_t *__restrict__ planes, const uint8_t *__restrict__ prep,
               const int64_t *__restrict__ bias, const uint32_t *__restrict__ offsets, uint32_t *__restrict__ out) {
     extern __shared__ __align__(16) uint8_t lds[];
@@ -916,7 +923,7 @@ constexpr int kWavePieces = 8;  // staged 16-byte pieces per lane (a halo has at
 
 // PL: staged pieces per lane (a 3x3 halo of 64-channel columns has at most 7 x 64)
 template <int NCB, bool GARBLE, int K33, int PL>
-__global__ void __launch_bounds__(kLinBlock) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ void __launch_bounds__(kLinBlock) __attribute__((amdgpu_waves_per_eu(2)))
 k_linear_gemm_w(const LinPlan L, const uint8_t *__restrict__ planes, const uint8_t *__restrict__ prep,
                 const int64_t *__restrict__ bias, const uint32_t *__restrict__ offsets, uint32_t *__restrict__ out) {
     extern __shared__ __align__(16) uint8_t lds[];
