@@ -501,4 +501,32 @@ void build_eval_plan(const Plan &P, EvalPlan *E) {
     E->nsteps = ns;
 }
 
+void build_split_plan(const Plan &P, SplitPlan *E) {
+    memset(E, 0, sizeof *E);
+    E->k = P.k;
+    E->G = P.G;
+    E->total_words = P.total_words;
+    E->work_words = P.work_words;
+    E->ntab = P.ntab;
+    E->gid = P.gid;
+    E->n = P.n;
+    E->a0 = P.a0;
+    for (uint32_t i = 0; i < P.k; ++i) E->mod[i] = P.mod[i];
+    uint32_t toff = 0;
+    for (uint32_t g = 0; g < P.G;) {
+        const uint32_t src = gate_src(P.gate[g]);
+        uint32_t r = 0, all = 0;
+        for (; g + r < P.G && gate_src(P.gate[g + r]) == src; ++r) {
+            const uint32_t d = P.gate[g + r];
+            const ModConst &mm = P.mod[gate_dst(d)];
+            E->gate[g + r] = d;
+            E->goff[g + r] = toff;
+            toff += (P.mod[src].m - 1) * mm.W;
+            if (mm.pad_amb == 0) all = 1;
+        }
+        E->run[E->nruns++] = g | (r << 8) | (all << 16) | (src << 20);
+        g += r;
+    }
+}
+
 }  // namespace redash

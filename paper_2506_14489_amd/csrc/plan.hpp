@@ -206,6 +206,36 @@ struct EvalPlan {
 // The evaluator's target-major schedule for a plan built by build_plan.
 void build_eval_plan(const Plan &P, EvalPlan *out);
 
+// ---------------------------------------------------------------------------
+// Gate list of the evaluators that split a gadget's gates (k_eval_split,
+// k_eval_small), by runs of gates that share a digit label: with a run's
+// bounds and every gate's table offset at hand, a wave goes straight to its
+// gates instead of walking the list (two dependent scalar loads per gate, about
+// a microsecond per run of 11).
+// ---------------------------------------------------------------------------
+// Per run: bits 0-7 first gate, 8-15 number of gates, 16 some gate's pad takes
+// all 256 bits (pad_amb 0), 20-23 the digit's modulus index.
+constexpr uint32_t rn_first(uint32_t r) { return r & 255u; }
+constexpr uint32_t rn_gates(uint32_t r) { return (r >> 8) & 255u; }
+constexpr uint32_t rn_all(uint32_t r) { return (r >> 16) & 1u; }
+constexpr uint32_t rn_src(uint32_t r) { return (r >> 20) & 15u; }
+constexpr int kMaxRuns = 32;  // at most t + u = k Phase-A and Phase-B digits: k <= 15
+
+struct SplitPlan {
+    uint32_t k, G;
+    uint32_t total_words, work_words;
+    uint32_t ntab, nruns;
+    uint32_t gid;
+    uint64_t n, a0;
+    ModConst mod[kMaxK];
+    uint32_t gate[kMaxGates];  // as in Plan
+    uint32_t goff[kMaxGates];  // word offset of the gate's table block in units of n words
+    uint32_t run[kMaxRuns];
+};
+
+// The runs of a plan built by build_plan.
+void build_split_plan(const Plan &P, SplitPlan *out);
+
 // A modulus the library accepts: a prime or a power of two in 2..255.
 bool modulus_ok(uint32_t m);
 

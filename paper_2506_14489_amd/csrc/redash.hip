@@ -100,7 +100,7 @@ __device__ __forceinline__ uint32_t free_op_entries(uint32_t lane, uint32_t kind
 
 // Fills the free-operation tables (gates 0..ntab-1 that have one).  Wave w
 // fills gates w, w + waves, ...
-__device__ __forceinline__ void stage_free_op_tables(const Plan &P, uint32_t *lds, int tid, uint32_t nwaves) {
+__device__ __forceinline__ void stage_free_op_tables(const SplitPlan &P, uint32_t *lds, int tid, uint32_t nwaves) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(tid) / 64u);
     const uint32_t lane = static_cast<uint32_t>(tid) % 64u;
     for (uint32_t g = wave; g < P.ntab; g += nwaves) {
@@ -451,12 +451,12 @@ struct SplitLaunch {
     uint32_t split0;  // waves per 64 gadgets in them (2, 4 or 12)
     uint32_t split1;  // waves per 64 gadgets in the others
 };
-static_assert(sizeof(Plan) + 4 * sizeof(void *) + sizeof(SplitLaunch) <= 4096,
+static_assert(sizeof(SplitPlan) + 4 * sizeof(void *) + sizeof(SplitLaunch) <= 4096,
               "the split evaluator's arguments fit the kernel argument block");
 
 template <int BLOCK>
 __global__ void __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kEvalWaves, kEvalWaves)))
-k_eval_split(const Plan P, const uint32_t *__restrict__ in, const uint32_t *__restrict__ tab, uint32_t *out,
+k_eval_split(const SplitPlan P, const uint32_t *__restrict__ in, const uint32_t *__restrict__ tab, uint32_t *out,
              uint32_t *work, const SplitLaunch L) {
     extern __shared__ uint32_t lds[];
     uint32_t *K = lds + kTableRegionBytes / 4;
@@ -478,12 +478,9 @@ k_eval_split(const Plan P, const uint32_t *__restrict__ in, const uint32_t *__re
     const bool live = a < P.n;  // dead lanes still take every barrier
     const LabelBufs LB{in, out, work, P.n, static_cast<uint32_t>(live ? a : 0) * 4u};
     const uint64_t tau0 = (P.a0 + a) * P.G;
-    uint64_t toff = 0;  // table offset of gate g
-    for (uint32_t g = 0; g < P.G;) {
-        const uint32_t src = gate_src(P.gate[g]);
-        uint32_t r = 1;
-        while (g + r < P.G && gate_src(P.gate[g + r]) == src) ++r;
-        const ModConst mq = P.mod[src];
+    for (uint32_t run = 0; run < P.nruns; ++run) {
+        const uint32_t rd = P.run[run], g = rn_first(rd), r = rn_gates(rd);
+        const ModConst mq = P.mod[rn_src(rd)];
         const uint32_t q = mq.m;
         // Every gate of the run hashes the same digit label: the wave reads,
         // folds and colours it once per run.
@@ -499,30 +496,192 @@ k_eval_split(const Plan P, const uint32_t *__restrict__ in, const uint32_t *__re
             colour = w0 & mq.mask;
             if (colour >= q) colour = 0;
         }
-        for (uint32_t i = 0; i < r; ++i) {
+        for (uint32_t i = part; i < r; i += split) {
+            if (!live) continue;  // (a lane's choice: the loop itself stays uniform)
             const uint32_t d = P.gate[g + i];
-            if (i % split == part && live) {
-                const ModConst mm = P.mod[gate_dst(d)];
-                const uint32_t Wd = mm.W;
-                // the row (right-aligned, as the register labels)
-                uint32_t row[kMaxW];
-                static_for<kMaxW>([&](auto p) { row[p] = 0; });
-                if (colour != 0) load_row(row, tab + toff + (a * (q - 1) + (colour - 1)) * Wd, Wd);
-                uint32_t T[kMaxW];
-                load_label(T, LB, gate_tsrc(d), mm, gate_tsrc(d) != kLocZero);
-                uint32_t Vn[1][8], D[kMaxW];
-                hash_pairs<1>(TT, LdsKey{K}, x, [&] { return opaque64(tau0 + g + i); }, P.gid, mm.pad_amb == 0, Vn);
-                gate_pad(TT, K, P.gid, mm, Vn[0], D,
-                         [&](uint32_t(&f)[4]) { static_for<4>([&](auto l) { f[l] = x[l]; }); },
-                         [&] { return tau0 + g + i; });
-                const uint32_t e = gate_dst(d) | (gate_kind(d) << 4) | (gate_tab(d) << 5) | (gate_coeff(d) << 6);
-                reg_update(g + i, e, mm, D, row, T);
-                store_label(T, LB, gate_tdst(d), mm);
-            }
-            toff += P.n * (q - 1) * P.mod[gate_dst(d)].W;
+            const ModConst mm = P.mod[gate_dst(d)];
+            const uint32_t Wd = mm.W;
+            // the row (right-aligned, as the register labels)
+            uint32_t row[kMaxW];
+            static_for<kMaxW>([&](auto p) { row[p] = 0; });
+            if (colour != 0)
+                load_row(row, tab + static_cast<uint64_t>(P.goff[g + i]) * P.n + (a * (q - 1) + (colour - 1)) * Wd, Wd);
+            uint32_t T[kMaxW];
+            load_label(T, LB, gate_tsrc(d), mm, gate_tsrc(d) != kLocZero);
+            uint32_t Vn[1][8], D[kMaxW];
+            hash_pairs<1>(TT, LdsKey{K}, x, [&] { return opaque64(tau0 + g + i); }, P.gid, mm.pad_amb == 0, Vn);
+            gate_pad(TT, K, P.gid, mm, Vn[0], D,
+                     [&](uint32_t(&f)[4]) { static_for<4>([&](auto l) { f[l] = x[l]; }); },
+                     [&] { return tau0 + g + i; });
+            const uint32_t e = gate_dst(d) | (gate_kind(d) << 4) | (gate_tab(d) << 5) | (gate_coeff(d) << 6);
+            reg_update(g + i, e, mm, D, row, T);
+            store_label(T, LB, gate_tdst(d), mm);
         }
         __syncthreads();
-        g += r;
+    }
+}
+
+// The free operation of gate g (descriptor d) on one packed word of its label
+// (reg_update for a single word w, which may differ between lanes): Dw the
+// pad's digits of that word, rw the row's, l the label's.
+__device__ __forceinline__ uint32_t word_update(uint32_t g, uint32_t d, const ModConst &mm, uint32_t Dw, uint32_t rw,
+                                                uint32_t l, uint32_t w) {
+    const bool acc = gate_kind(d) != 0;
+    const uint32_t coeff = gate_coeff(d);
+    if (mm.m == 2) return !acc || (coeff & 1u) ? l ^ Dw ^ rw : l;
+    const bool last = w + 1 == mm.W;
+    if (!mm.fast) {
+        const uint32_t nres = last ? mm.glast : mm.g;
+        uint32_t res = 0, D = Dw;
+        for (uint32_t j = nres; j-- > 0;) {
+            uint32_t pd = D;
+            if (j) {
+                const uint32_t qd = div_m(D, mm);
+                pd = D - qd * mm.m;
+                D = qd;
+            }
+            const uint32_t ev = add_mod(pd, field(rw, j, mm), mm.m), lj = field(l, j, mm);
+            const uint32_t v = acc ? add_mod(lj, mul_mod(coeff, ev, mm), mm.m) : mul_mod(coeff, sub_mod(lj, ev, mm.m), mm);
+            res |= v << (mm.b * j);
+        }
+        return res;
+    }
+    const uint32_t cc = acc ? coeff : mm.m - coeff;
+    const uint32_t lmask = opaque(acc ? 0u : 0xffffffffu), km = opaque(acc ? 0u : mm.sw_ones * mm.m);
+    const uint64_t tk = opaque64(static_cast<uint64_t>(kEvalTableBase + g * kTableBytes) << 32);
+    uint32_t res = 0;
+    // the full words' lanes, then the last word's (one copy of the shapes)
+#pragma unroll 1
+    for (uint32_t k = 0; k < 2; ++k) {
+        const uint32_t nres = k ? mm.glast : mm.g, nlo = k ? mm.nlo_l : mm.nlo_f, lo_M = k ? mm.lo_M_l : mm.lo_M_f;
+        const uint32_t lo_s = k ? mm.lo_s_l : mm.lo_s_f, pw_lo = k ? mm.pw_lo_l : mm.pw_lo_f;
+        const uint32_t c_hi = k ? mm.fc_hi_l : mm.fc_hi_f, c_lo = k ? mm.fc_lo_l : mm.fc_lo_f;
+        if (last == (k == 1)) {
+            res = gate_tab(d) ? fast_word_any<true>(Dw, nres, nlo, lo_M, lo_s, pw_lo, c_hi, c_lo, rw, l, lmask, km, acc,
+                                                    cc, mm, tk)
+                              : fast_word_any<false>(Dw, nres, nlo, lo_M, lo_s, pw_lo, c_hi, c_lo, rw, l, lmask, km,
+                                                     acc, cc, mm, 0);
+        }
+    }
+    return acc ? swar_add(l, res & mm.sw_even, (res >> mm.b) & mm.sw_even, mm) : res;
+}
+
+// ---------------------------------------------------------------------------
+// The evaluator for the smallest calls: at most kSmallMost gadgets per CU.
+// A run of gates is two steps with a barrier after each.  Hash: a lane per
+// (gate, gadget), so a wave's table reads serve 64 hashes where a wave per
+// gate would serve as many as the workgroup has gadgets.  Update: a lane per
+// (gadget, packed word), a wave (or two) per gate, whose modulus stays uniform;
+// the full words and the last word take their shapes in two passes.  Every
+// label of the workgroup's gadgets stays in LDS from the input to the output,
+// and a run's rows are requested before its hashes.
+// ---------------------------------------------------------------------------
+// (12 primes, 77 gates: 1,000 gadgets 98 -> 66 us, 5,120 99 -> 79; one past,
+// 84 us on the 12-wave split.)
+constexpr uint32_t kSmallMost = 20;  // 6 words of 20 gadgets: two waves per gate
+constexpr int kSmallTasks = 3;       // update waves per wave and run: 14 gates x 2 over 12 waves
+
+struct SmallLaunch {
+    uint32_t per;  // gadgets per workgroup, at most kSmallMost
+};
+
+// LDS words after the free-operation tables: the three label areas, then the
+// hash fractions of a run's gates (8 limbs each).
+__host__ __device__ constexpr uint32_t small_lds_words(uint32_t total_words, uint32_t work_words, uint32_t k,
+                                                       uint32_t per) {
+    return (2 * total_words + work_words) * per + 8 * k * per;
+}
+
+template <int BLOCK>
+__global__ void __launch_bounds__(BLOCK)
+k_eval_small(const SplitPlan P, const uint32_t *__restrict__ in, const uint32_t *__restrict__ tab,
+             uint32_t *__restrict__ out, const SmallLaunch L) {
+    extern __shared__ uint32_t lds[];
+    uint32_t *K = lds + kTableRegionBytes / 4;
+    const uint32_t tid = threadIdx.x, lane = tid % 64;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid / 64), c = L.per;
+    uint32_t *lin = lds + (kEvalTableBase + P.ntab * kTableBytes) / 4;
+    uint32_t *lout = lin + P.total_words * c, *lwork = lout + P.total_words * c, *Vb = lwork + P.work_words * c;
+    const uint32_t a0 = blockIdx.x * c;  // the workgroup's first gadget
+    const uint32_t nlive = P.n - a0 < c ? static_cast<uint32_t>(P.n - a0) : c;
+    for (uint32_t e = tid; e < P.total_words * c; e += BLOCK) {
+        const uint32_t w = e / c, gl = e % c;
+        lin[e] = gl < nlive ? in[static_cast<uint64_t>(w) * P.n + a0 + gl] : 0u;
+    }
+    stage_perm_te02(lds, tid, BLOCK);
+    stage_hash_key(K, tid, BLOCK);
+    stage_free_op_tables(P, lds, tid, BLOCK / 64);
+    const PermTE02 TT = perm_te02();
+    // word 0 of modulus mc's labels in place `loc` (word w of gadget gl: [w c + gl])
+    auto place = [&](uint32_t loc, const ModConst &mc) -> uint32_t * {
+        return loc == kLocIn ? lin + mc.woff * c : loc == kLocOut ? lout + mc.woff * c : lwork + mc.wkoff * c;
+    };
+    for (uint32_t run = 0; run < P.nruns; ++run) {
+        const uint32_t rd = P.run[run], g = rn_first(rd), r = rn_gates(rd), src = rn_src(rd), d0 = P.gate[g];
+        const bool all = rn_all(rd) != 0;
+        const uint32_t q = P.mod[src].m, Wq = P.mod[src].W, qmask = P.mod[src].mask;
+        __syncthreads();  // the labels of the run before (or of the input) are in place
+        const uint32_t *dig = place(gate_dsrc(d0), P.mod[src]);
+        auto digit = [&](uint32_t gl, uint32_t(&x)[4]) {
+            static_for<4>([&](auto l) { x[l] = 0; });
+            static_for<kMaxW>([&](auto w) {
+                if (w < static_cast<int>(Wq)) x[w & 3] ^= dig[w * c + gl];
+            });
+        };
+        // The rows of this wave's update tasks: task t = wave, wave + 12, ...
+        // is gate t / wpg of the run, its lane (t % wpg) 64 + lane the pair
+        // (word, gadget).
+        const uint32_t wpg = kMaxW * c > 64 ? 2u : 1u;
+        uint32_t row[kSmallTasks];
+        static_for<kSmallTasks>([&](auto u) {
+            row[u] = 0;
+            const uint32_t t = wave + u * (BLOCK / 64), i = t / wpg, idx = (t % wpg) * 64 + lane;
+            if (i < r) {
+                const uint32_t W = P.mod[gate_dst(P.gate[g + i])].W, w = idx / c, gl = idx % c;
+                if (w < W && gl < nlive) {
+                    uint32_t colour = dig[gl] & qmask;
+                    if (colour >= q) colour = 0;
+                    if (colour != 0)
+                        row[u] = tab[static_cast<uint64_t>(P.goff[g + i]) * P.n +
+                                     (static_cast<uint64_t>(a0 + gl) * (q - 1) + colour - 1) * W + w];
+                }
+            }
+        });
+        // Hashes: job i c + gl is gate g + i of gadget gl.
+        if (wave * 64 < r * c) {
+            const uint32_t job = tid < r * c ? tid : r * c - 1, i = job / c, gl = job % c;
+            uint32_t x[4], V[1][8];
+            digit(gl, x);
+            hash_pairs<1>(TT, LdsKey{K}, x, [&] { return opaque64((P.a0 + a0 + gl) * P.G + g + i); }, P.gid, all, V);
+            if (tid < r * c) static_for<8>([&](auto l) { Vb[l * (r * c) + job] = V[0][l]; });
+        }
+        __syncthreads();
+        // Updates.
+        static_for<kSmallTasks>([&](auto u) {
+            const uint32_t t = wave + u * (BLOCK / 64), i = t / wpg, idx = (t % wpg) * 64 + lane;
+            if (i < r) {
+                const uint32_t d = P.gate[g + i];
+                const ModConst mm = P.mod[gate_dst(d)];
+                const uint32_t w = idx / c, gl = idx % c;
+                if (w < mm.W) {
+                    uint32_t V[8], D[kMaxW];
+                    static_for<8>([&](auto l) { V[l] = Vb[l * (r * c) + i * c + gl]; });
+                    gate_pad(TT, K, P.gid, mm, V, D, [&](uint32_t(&x)[4]) { digit(gl, x); },
+                             [&] { return (P.a0 + a0 + gl) * P.G + g + i; });
+                    const uint32_t at = w + label_off(mm);
+                    uint32_t Dw = 0;
+                    static_for<kMaxW>([&](auto p) { Dw = at == static_cast<uint32_t>(p) ? D[p] : Dw; });
+                    uint32_t l = 0;
+                    if (gate_tsrc(d) != kLocZero) l = place(gate_tsrc(d), mm)[w * c + gl];
+                    place(gate_tdst(d) ? kLocWork : kLocOut, mm)[w * c + gl] = word_update(g + i, d, mm, Dw, row[u], l, w);
+                }
+            }
+        });
+    }
+    __syncthreads();
+    for (uint32_t e = tid; e < P.total_words * c; e += BLOCK) {
+        const uint32_t w = e / c, gl = e % c;
+        if (gl < nlive) out[static_cast<uint64_t>(w) * P.n + a0 + gl] = lout[e];
     }
 }
 
@@ -932,10 +1091,11 @@ int device_info(DeviceInfo *out) {
 // equal bytes are equal parameters; unused entries that differ only cost a
 // rebuild.)
 struct PlanCache {
-    bool valid, has_eval;
+    bool valid, has_eval, has_split;
     redash_params p;
     Plan P;
     EvalPlan E;
+    SplitPlan S;
 };
 thread_local PlanCache t_plan;
 
@@ -948,7 +1108,7 @@ int cached_plan(const redash_params *p, const Plan **out) {
         if (rc) return rc;
         c.p = *p;
         c.valid = true;
-        c.has_eval = false;
+        c.has_eval = c.has_split = false;
     }
     *out = &c.P;
     return REDASH_OK;
@@ -967,6 +1127,21 @@ const EvalPlan &eval_plan(const Plan &P) {
         c.has_eval = true;
     }
     return c.E;
+}
+
+// The runs of P, likewise.
+const SplitPlan &split_plan(const Plan &P) {
+    PlanCache &c = t_plan;
+    if (&P != &c.P) {  // not reached, as above
+        static thread_local SplitPlan S;
+        build_split_plan(P, &S);
+        return S;
+    }
+    if (!c.has_split) {
+        build_split_plan(c.P, &c.S);
+        c.has_split = true;
+    }
+    return c.S;
 }
 
 // Threads per workgroup for n gadgets: the smallest multiple of 64 that keeps
@@ -1008,7 +1183,7 @@ int launched() {
 }
 
 // Launches k_eval_split (it may use more than 64 KiB of LDS).
-int launch_split_kernel(const Plan &P, uint32_t lds, const uint32_t *in, const uint32_t *tab, uint32_t *out,
+int launch_split_kernel(const SplitPlan &P, uint32_t lds, const uint32_t *in, const uint32_t *tab, uint32_t *out,
                         uint32_t *work, const SplitLaunch &L, unsigned grid, int threads, hipStream_t stream) {
     const int rc = allow_lds(reinterpret_cast<const void *>(&k_eval_split<kEvalBlock>), lds);
     if (rc) return rc;
@@ -1022,7 +1197,7 @@ constexpr uint32_t split_most(uint32_t split) { return kEvalBlock / split / 64 *
 
 // k_eval_split over gadgets first .. first + count - 1 (of the plan's n), each
 // group of 64 gadgets on `split` waves (12, 4 or 2).
-int launch_split(uint32_t split, const Plan &P, uint32_t lds, const uint32_t *in, const uint32_t *tab, uint32_t *out,
+int launch_split(uint32_t split, const SplitPlan &P, uint32_t lds, const uint32_t *in, const uint32_t *tab, uint32_t *out,
                  uint32_t *work, uint64_t first, uint64_t count, hipStream_t stream) {
     int per = 0;
     const int rc = block_for(count, static_cast<int>(split_most(split)), &per);
@@ -1042,7 +1217,8 @@ uint32_t split_for(uint64_t count, uint64_t cus) {
     return 0;
 }
 
-// Launches the evaluators for n gadgets.  A call that one round of two
+// Launches the evaluators for n gadgets.  A call of at most kSmallMost gadgets
+// per CU runs on k_eval_small.  A call that one round of two
 // workgroups per CU holds when a gadget takes 12, 4 or 2 waves runs on
 // k_eval_split with that split (runs of gates sharing a digit have at most
 // k - 1 gates, 11 on the 12-prime base: with 12 waves one gate per wave and
@@ -1068,18 +1244,28 @@ int launch_eval(const Plan &P, uint32_t lds, const uint32_t *in, const uint32_t 
     int rc = device_info(&d);
     if (rc) return rc;
     const uint64_t ncu = static_cast<uint64_t>(d.cus);
+    if (P.n <= ncu * kSmallMost) {
+        const uint32_t per = static_cast<uint32_t>((P.n + ncu - 1) / ncu);
+        const uint32_t bytes = lds + 4 * small_lds_words(P.total_words, P.work_words, P.k, per);
+        if (bytes <= static_cast<uint32_t>(d.max_lds)) {
+            if ((rc = allow_lds(reinterpret_cast<const void *>(&k_eval_small<kEvalBlock>), bytes))) return rc;
+            hipLaunchKernelGGL(k_eval_small<kEvalBlock>, dim3(grid_for(P.n, static_cast<int>(per))), dim3(kEvalBlock),
+                               bytes, stream, split_plan(P), in, tab, out, SmallLaunch{per});
+            return launched();
+        }
+    }
     for (const uint32_t split : {4u, 2u}) {
         const uint32_t per0 = split_most(split);
         const uint64_t full = 2 * ncu * per0;
         if (P.n > full && P.n - full <= ncu * 64) {
             const uint32_t nb0 = static_cast<uint32_t>(2 * ncu);
             const unsigned grid = nb0 + grid_for(P.n - full, 64);
-            return launch_split_kernel(P, lds, in, tab, out, work, SplitLaunch{0, nb0, split, 12}, grid, kEvalBlock,
+            return launch_split_kernel(split_plan(P), lds, in, tab, out, work, SplitLaunch{0, nb0, split, 12}, grid, kEvalBlock,
                                        stream);
         }
     }
     if (const uint32_t split = split_for(P.n, ncu))
-        return launch_split(split, P, lds, in, tab, out, work, 0, P.n, stream);
+        return launch_split(split, split_plan(P), lds, in, tab, out, work, 0, P.n, stream);
     const uint64_t round = 2 * ncu * kLaneBlock;  // gadgets of one round, one per lane
     uint64_t bulk = P.n;
     const uint64_t rest = P.n % round;
@@ -1092,7 +1278,7 @@ int launch_eval(const Plan &P, uint32_t lds, const uint32_t *in, const uint32_t 
                        work);
     if ((rc = launched())) return rc;
     if (bulk == P.n) return REDASH_OK;
-    return launch_split(split_for(P.n - bulk, ncu), P, lds, in, tab, out, work, bulk, P.n - bulk, stream);
+    return launch_split(split_for(P.n - bulk, ncu), split_plan(P), lds, in, tab, out, work, bulk, P.n - bulk, stream);
 }
 
 

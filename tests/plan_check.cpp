@@ -277,6 +277,29 @@ static void check_schedule(const uint32_t *moduli, uint32_t k, const uint32_t *S
     static EvalPlan E;
     build_eval_plan(P, &E);
     CHECK(sizeof(EvalPlan) <= 4096, "EvalPlan of %zu bytes exceeds the kernel-argument limit", sizeof(EvalPlan));
+    // the runs of the split evaluators: every gate once and in order, one digit
+    // per run, table offsets as the gate blocks lie
+    {
+        static SplitPlan R;
+        build_split_plan(P, &R);
+        CHECK(R.nruns <= kMaxRuns && R.nruns >= 1, "runs k=%u t=%u: %u", k, t, R.nruns);
+        uint32_t g = 0, off = 0;
+        for (uint32_t i = 0; i < R.nruns; ++i) {
+            CHECK(rn_first(R.run[i]) == g && rn_gates(R.run[i]) >= 1 && rn_gates(R.run[i]) < k, "run %u", i);
+            uint32_t all = 0, dsts = 0;
+            for (uint32_t j = 0; j < rn_gates(R.run[i]); ++j, ++g) {
+                const uint32_t d = P.gate[g];
+                CHECK(R.gate[g] == d && gate_src(d) == rn_src(R.run[i]) && R.goff[g] == off, "run %u gate %u", i, g);
+                CHECK(!(dsts & (1u << gate_dst(d))) && gate_dsrc(d) == gate_dsrc(P.gate[rn_first(R.run[i])]),
+                      "run %u gate %u: one place for the digit, a destination each", i, g);
+                dsts |= 1u << gate_dst(d);
+                off += (P.mod[gate_src(d)].m - 1) * P.mod[gate_dst(d)].W;
+                if (P.mod[gate_dst(d)].pad_amb == 0) all = 1;
+            }
+            CHECK(rn_all(R.run[i]) == all, "run %u all", i);
+        }
+        CHECK(g == P.G, "runs cover %u of %u gates", g, P.G);
+    }
     // every gate exactly once
     uint32_t used[kMaxGates] = {};
     for (uint32_t st = 0; st < E.nsteps; ++st) {

@@ -595,6 +595,27 @@ def test_one_gadget_per_lane_past_the_round_and_rest_on_varied_bases(name, modul
     _check_full(w, 2048, 2048, 2048, 8)
 
 
+# The smallest calls: up to 20 gadgets per CU share a workgroup (a lane per gate
+# and gadget hashes, a lane per gadget and word updates; above 10 gadgets the
+# words of a gate take two waves).  (name, base, scaling, gadgets per CU, extra)
+SMALL_CALLS = [("one", tuple(WL.PRIMES_12), (11,), 0, 1), ("ragged", (2, 3, 5, 7, 11), (0, 4), 0, 63),
+               ("one-wave-last", tuple(WL.PRIMES_12), (0, 5), 10, 0),
+               ("two-waves-first", (3, 5, 7, 8, 11, 13, 17, 19), (3,), 10, 1),
+               ("last", tuple(WL.PRIMES_12), (10, 11), 20, 0), ("past-last", (2, 3, 5, 7, 11), (4,), 20, 1),
+               ("k15", tuple(rns.first_primes(15)), (13, 14), 1, 5), ("generic", (4, 47, 53, 59), (1,), 3, 2),
+               ("generic-16", (5, 13, 16, 41), (2,), 12, 0), ("large", (32, 167, 173), (0,), 19, 7),
+               ("loops-251", (2, 97, 251), (2,), 4, 0)]
+
+
+@pytest.mark.parametrize("name,moduli,S,per_cu,extra", SMALL_CALLS, ids=[e[0] for e in SMALL_CALLS])
+def test_small_calls(name, moduli, S, per_cu, extra):
+    n = torch.cuda.get_device_properties(0).multi_processor_count * per_cu + extra
+    P = rns.cardinality(moduli)
+    w = WL.Workload(f"small-{name}", tuple(moduli), tuple(S), n, 120 + per_cu + extra, "uniform", -(P // 2),
+                    P - P // 2)
+    _check_full(w, 2048, 2048, 2048, 4)
+
+
 # The garbler gives 64 gadgets 8, 4, 2 or 1 waves, as many as one round of two
 # workgroups of 8 waves per CU holds: the last call of each size and one past it.
 @pytest.mark.parametrize("per,extra", [(64, 0), (64, 1), (128, 0), (128, 1), (256, 0), (256, 1)])
