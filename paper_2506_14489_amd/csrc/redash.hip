@@ -952,81 +952,92 @@ k_garble(const Plan P, const SeedKey key, const uint32_t *__restrict__ offsets, 
 // ---------------------------------------------------------------------------
 // Encode (stand-in for oblivious transfer) and decode.
 // ---------------------------------------------------------------------------
-template <int BLOCK>
-__global__ void __launch_bounds__(BLOCK) k_encode(const Plan P, const int64_t *__restrict__ x,
-                                                  const uint32_t *__restrict__ zero,
-                                                  const uint32_t *__restrict__ offsets, uint32_t *__restrict__ lab) {
-    __shared__ uint32_t Rl[kMaxK * kMaxW];
-    for (uint32_t i = threadIdx.x; i < P.total_words; i += BLOCK) Rl[i] = offsets[i];
-    __syncthreads();
-    const uint64_t a = static_cast<uint64_t>(blockIdx.x) * BLOCK + threadIdx.x;
+// x mod m of a signed 64-bit x: (hi 2^32 + lo) mod m by halves, 2^64 mod m
+// taken off for a negative x.
+__device__ __forceinline__ uint32_t mod64(int64_t x, uint32_t m) {
+    const uint32_t lo = static_cast<uint32_t>(x), hi = static_cast<uint32_t>(static_cast<uint64_t>(x) >> 32);
+    const uint32_t t = (0xffffffffu % m + 1u) % m;  // 2^32 mod m
+    uint32_t r = ((hi % m) * t + lo % m) % m;       // below 2^16 + 2^8
+    if (x < 0) r = (r + m * m - (t * t) % m) % m;   // 2^64 mod m = t^2 mod m
+    return r;
+}
+
+// The index of this workgroup's 64 gadgets (grid_of_64: rows of 2^18, so that
+// no dimension reaches 2^32 work-items at 15 waves a workgroup).
+__device__ __forceinline__ uint64_t group64() {
+    return static_cast<uint64_t>(blockIdx.y) * (1u << 18) + blockIdx.x;
+}
+
+// A workgroup takes 64 gadgets and one wave per modulus (at most 15): the
+// modulus stays uniform in a wave and a small call still fills waves (65,536
+// gadgets over 10 primes: 49 us with every modulus of a gadget on one lane).
+// P is a multiple of m_i: (x mod P) mod m_i = x mod m_i.
+__global__ void __launch_bounds__(64 * kMaxK) k_encode(const Plan P, const int64_t *__restrict__ x,
+                                                       const uint32_t *__restrict__ zero,
+                                                       const uint32_t *__restrict__ offsets, uint32_t *__restrict__ lab) {
+    const uint32_t i = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    const uint64_t a = group64() * 64 + threadIdx.x % 64;
     if (a >= P.n) return;
     const uint64_t n = P.n;
-    int64_t r = x[a] % static_cast<int64_t>(P.P);
-    if (r < 0) r += static_cast<int64_t>(P.P);
-    for (uint32_t i = 0; i < P.k; ++i) {
-        const ModConst &mc = P.mod[i];
-        const uint32_t v = static_cast<uint32_t>(static_cast<uint64_t>(r) % mc.m);
-        const uint64_t base = static_cast<uint64_t>(mc.woff) * n + a;
-        for (uint32_t w = 0; w < mc.W; ++w)
-            lab[base + static_cast<uint64_t>(w) * n] = label_axpy(zero[base + static_cast<uint64_t>(w) * n],
-                                                                  Rl[mc.woff + w], v, w, mc);
-    }
+    const ModConst mc = P.mod[i];
+    const uint32_t v = mod64(x[a], mc.m);
+    const uint64_t base = static_cast<uint64_t>(mc.woff) * n + a;
+    for (uint32_t w = 0; w < mc.W; ++w)
+        lab[base + static_cast<uint64_t>(w) * n] =
+            label_axpy(zero[base + static_cast<uint64_t>(w) * n], offsets[mc.woff + w], v, w, mc);
 }
 
 __global__ void k_zero_u64(uint64_t *p) { *p = 0; }
 
-template <int BLOCK>
-__global__ void __launch_bounds__(BLOCK) k_decode(const Plan P, const uint32_t *__restrict__ Y,
-                                                  const uint32_t *__restrict__ O, const uint32_t *__restrict__ offsets,
-                                                  int64_t *__restrict__ y, unsigned long long *__restrict__ bad) {
-    __shared__ uint32_t Rl[kMaxK * kMaxW];
-    for (uint32_t i = threadIdx.x; i < P.total_words; i += BLOCK) Rl[i] = offsets[i];
-    __syncthreads();
-    const uint64_t a = static_cast<uint64_t>(blockIdx.x) * BLOCK + threadIdx.x;
-    if (a >= P.n) return;
+// The CRT of the base: value = sum over i of (v_i c_i mod m_i) P / m_i, mod P,
+// c_i = (P / m_i)^-1 mod m_i.
+struct CrtConst {
+    uint64_t quot[kMaxK];  // P / m_i
+    uint32_t inv[kMaxK];   // c_i
+};
+static_assert(sizeof(Plan) + sizeof(CrtConst) + 5 * sizeof(void *) <= 4096, "decode's arguments fit the argument block");
+
+// Workgroups as k_encode's: wave i checks the labels over modulus i and finds
+// their value; then one wave sums the CRT terms of its 64 gadgets (every
+// partial sum reduced below P < 2^63) and counts the bad ones.
+__global__ void __launch_bounds__(64 * kMaxK) k_decode(const Plan P, const CrtConst C, const uint32_t *__restrict__ Y,
+                                                       const uint32_t *__restrict__ O,
+                                                       const uint32_t *__restrict__ offsets, int64_t *__restrict__ y,
+                                                       unsigned long long *__restrict__ bad) {
+    __shared__ uint32_t term[kMaxK * 64];  // v_i c_i mod m_i, bit 31: the label is not O + v R
+    const uint32_t i = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+    const uint64_t a = group64() * 64 + lane;
     const uint64_t n = P.n;
-    bool ok = true;
-    uint32_t v[kMaxK];
-    for (uint32_t i = 0; i < P.k; ++i) {
-        const ModConst &mc = P.mod[i];
+    if (a < n) {
+        const ModConst mc = P.mod[i];
         const uint64_t base = static_cast<uint64_t>(mc.woff) * n + a;
         const uint32_t y0 = Y[base] & mc.mask, o0 = O[base] & mc.mask;
-        const uint32_t vi = mul_mod(sub_mod(y0, o0, mc.m), inverse_unit(Rl[mc.woff] & mc.mask, mc), mc);
+        const uint32_t vi = mul_mod(sub_mod(y0, o0, mc.m), inverse_unit(offsets[mc.woff] & mc.mask, mc), mc);
+        bool ok = true;
         for (uint32_t w = 0; w < mc.W; ++w) {
             const uint64_t at = base + static_cast<uint64_t>(w) * n;
-            if (label_axpy(O[at], Rl[mc.woff + w], vi, w, mc) != Y[at]) ok = false;
+            if (label_axpy(O[at], offsets[mc.woff + w], vi, w, mc) != Y[at]) ok = false;
         }
-#pragma unroll
-        for (int j = 0; j < kMaxK; ++j)
-            if (j == static_cast<int>(i)) v[j] = vi;
+        // (a malformed label's value may be m or more: reduced for the sum)
+        term[i * 64 + lane] = ((vi % mc.m) * C.inv[i]) % mc.m | (ok ? 0u : 0x80000000u);
     }
-    // Garner: mixed-radix digits d_i of the CRT value, then y = sum d_i prod_{l<i} m_l.
-    uint64_t val = 0, weight = 1;
-    uint32_t dig[kMaxK];
-#pragma unroll
-    for (int i = 0; i < kMaxK; ++i) {
-        if (i < static_cast<int>(P.k)) {
-            const ModConst &mc = P.mod[i];
-            uint32_t cur = 0, wmod = 1 % mc.m;  // sum_{j<i} d_j prod_{l<j} m_l  (mod m_i)
-#pragma unroll
-            for (int j = 0; j < kMaxK; ++j) {
-                if (j < i) {
-                    cur = add_mod(cur, mul_mod(dig[j] % mc.m, wmod, mc), mc.m);
-                    wmod = mul_mod(wmod, P.mod[j].m % mc.m, mc);
-                }
-            }
-            // wmod = prod_{l<i} m_l mod m_i, a unit since the base is coprime
-            dig[i] = mul_mod(sub_mod(v[i], cur, mc.m), inverse_unit(wmod, mc), mc);
-            val += static_cast<uint64_t>(dig[i]) * weight;
-            weight *= mc.m;
-        }
+    __syncthreads();
+    if (i != 0 || a >= n) return;
+    uint64_t val = 0;
+    uint32_t flags = 0;
+    for (uint32_t j = 0; j < P.k; ++j) {
+        const uint32_t t = term[j * 64 + lane];
+        flags |= t;
+        val += static_cast<uint64_t>(t & 0xffu) * C.quot[j];  // t P / m < P: the sum is below 2 P < 2^64
+        if (val >= P.P) val -= P.P;
     }
     // signed range [-floor(P/2), ceil(P/2) - 1] (Sec. 2.4)
     int64_t out = static_cast<int64_t>(val);
     if (val >= (P.P + 1) / 2) out -= static_cast<int64_t>(P.P);
     y[a] = out;
-    if (!ok) atomicAdd(bad, 1ull);
+    const uint64_t wrong = __ballot(flags >> 31);
+    if (wrong && lane == static_cast<uint32_t>(__ffsll(static_cast<unsigned long long>(wrong)) - 1))
+        atomicAdd(bad, static_cast<unsigned long long>(__popcll(wrong)));
 }
 
 // ---------------------------------------------------------------------------
@@ -1174,6 +1185,13 @@ int allow_lds(const void *kernel, size_t bytes) {
                    hipSuccess
                ? REDASH_OK
                : REDASH_E_HIP;
+}
+
+// One workgroup per 64 gadgets, in rows of at most 2^18 (see group64).
+dim3 grid_of_64(uint64_t n) {
+    const uint64_t groups = (n + 63) / 64, row = 1u << 18;
+    return groups <= row ? dim3(static_cast<unsigned>(groups))
+                         : dim3(static_cast<unsigned>(row), static_cast<unsigned>((groups + row - 1) / row));
 }
 
 unsigned grid_for(uint64_t n, int block) { return static_cast<unsigned>((n + block - 1) / block); }
@@ -1375,7 +1393,7 @@ int redash_encode(const redash_params *p, const int64_t *d_x, const uint32_t *d_
     if (!d_offsets) return REDASH_E_NULL;
     if (P.n == 0) return REDASH_OK;
     if (!d_x || !d_in_zero || !d_in_labels) return REDASH_E_NULL;
-    hipLaunchKernelGGL(k_encode<256>, dim3(grid_for(P.n, 256)), dim3(256), 0, stream, P, d_x, d_in_zero, d_offsets,
+    hipLaunchKernelGGL(k_encode, grid_of_64(P.n), dim3(64 * P.k), 0, stream, P, d_x, d_in_zero, d_offsets,
                        d_in_labels);
     return launched();
 }
@@ -1459,7 +1477,13 @@ int redash_decode(const redash_params *p, const uint32_t *d_out_labels, const ui
     hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(1), 0, stream, reinterpret_cast<uint64_t *>(bad));
     if ((rc = launched())) return rc;
     if (P.n == 0) return REDASH_OK;
-    hipLaunchKernelGGL(k_decode<256>, dim3(grid_for(P.n, 256)), dim3(256), 0, stream, P, d_out_labels, d_out_zero,
+    CrtConst C;
+    memset(&C, 0, sizeof C);
+    for (uint32_t i = 0; i < P.k; ++i) {
+        C.quot[i] = P.P / P.mod[i].m;
+        C.inv[i] = inverse_mod(static_cast<uint32_t>(C.quot[i] % P.mod[i].m), P.mod[i].m);
+    }
+    hipLaunchKernelGGL(k_decode, grid_of_64(P.n), dim3(64 * P.k), 0, stream, P, C, d_out_labels, d_out_zero,
                        d_offsets, d_y, bad);
     return launched();
 }

@@ -595,6 +595,39 @@ def test_one_gadget_per_lane_past_the_round_and_rest_on_varied_bases(name, modul
     _check_full(w, 2048, 2048, 2048, 8)
 
 
+@pytest.mark.parametrize("moduli,S", [((2, 3, 5, 7, 11), (4,)), (tuple(rns.first_primes(15)), (0,)),
+                                      ((3, 64, 251), (1,)), ((2, 255 - 4), (0,))])
+def test_encode_reduces_any_value_and_decode_counts_each_bad_gadget(moduli, S):
+    """Values over the whole int64 range (encode takes them mod P), ragged
+    workgroups of 64 gadgets, and corrupted labels: one word of one modulus in
+    some gadgets, several moduli in others; each bad gadget counts once."""
+    n, P = 64 * 3 + 17, rns.cardinality(moduli)
+    bp, op = _params_pair(moduli, S, n, 77)
+    rng = np.random.default_rng(5)
+    x = rng.integers(-(1 << 63), (1 << 63) - 1, size=n, dtype=np.int64)
+    x[:6] = [-(1 << 63), (1 << 63) - 1, -1, 0, -(1 << 32), (1 << 32) - 1]
+    buf = B.Buffers(bp)
+    B.redash_garble_scale(bp, buf.offsets, buf.in_zero, buf.out_zero, buf.tables, buf.work)
+    xd = torch.from_numpy(x).cuda()
+    B.redash_encode(bp, xd, buf.in_zero, buf.offsets, buf.in_labels)
+    zin, offs = H.to_u32(buf.in_zero), H.to_u32(buf.offsets)
+    assert np.array_equal(H.to_u32(buf.in_labels), O.encode(op, x, zin, offs))
+    # decode the input labels under the input zero-labels: x mod P, signed
+    lab = buf.in_labels.clone()
+    lay, _ = H.label_layout(moduli)
+    for a in (0, 63, 64, n - 1):
+        lab[lay[0][0] * n + a] ^= 1
+    for woff, W in lay:
+        lab[(woff + W - 1) * n + 100] ^= 1
+    B.redash_decode(bp, lab, buf.in_zero, buf.offsets, buf.y, buf.bad)
+    torch.cuda.synchronize()
+    assert int(buf.bad.item()) == 5
+    want = [(int(v) + P // 2) % P - P // 2 for v in x]
+    good = [a for a in range(n) if a not in (0, 63, 64, n - 1, 100)]
+    y = buf.y.cpu().numpy()
+    assert [int(y[a]) for a in good] == [want[a] for a in good]
+
+
 # The smallest calls: up to 20 gadgets per CU share a workgroup (a lane per gate
 # and gadget hashes, a lane per gadget and word updates; above 10 gadgets the
 # words of a gate take two waves).  (name, base, scaling, gadgets per CU, extra)
