@@ -92,6 +92,7 @@ struct LinPlan {
     uint32_t lds_a, lds_b, lds_o, lds_bytes;
     uint32_t npairs;
     uint32_t word_split;          // k_linear_gemm: one workgroup per packed word (else per modulus)
+    uint32_t og_xcd;              // k_linear_gemm: output channel groups dealt to the XCDs (see the plan)
     uint32_t fold_c;              // column fold (see the plan): the layer's own c_in, else 0
     uint32_t flat, tile_rows;     // k_linear_gemm over the flattened plane (see the plan); rows of tiles
     uint64_t n_in, n_out;         // activations
@@ -258,20 +259,28 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     L->xw = (L->xt - 1) * L->lstep + L->kw;
     L->halo = L->kh * L->xw * L->xstride;
     L->tile_rows = L->rows;
-    // Flattened tiles for narrow rows (3x3, stride 1, several chunks, at
-    // most 8 output columns): output q = y wp + x of the padded plane reads
-    // q + dy wp + dx, so a tile of 16 consecutive q stages one run of
-    // 16 + 2 wp + 2 plane positions and reads tap (dy, dx) at offset
-    // dy wp + dx; outputs with x >= cols are dropped at the store.  A
-    // 16-position tile over a 7-position row otherwise leaves 9 of 16
-    // matrix columns idle.
+    // Flattened tiles (3x3, stride 1, several 64-channel chunks): output q =
+    // y wp + x of the padded plane reads q + dy wp + dx, so a tile of XT
+    // consecutive q stages one run of XT + 2 wp + 2 plane positions and reads
+    // tap (dy, dx) at offset dy wp + dx; outputs with x >= cols are dropped at
+    // the store.  Rows narrower than a tile leave no matrix columns idle that
+    // way, and the staged run of a 32-position tile fits two workgroups per CU
+    // up to 38 plane columns: a stage's weights (36 KB for four residues and a
+    // chunk) then serve twice the positions.  16 where 32 would leave too few
+    // workgroups (7x7 over 8 groups of outputs: 1,008, 0.268 ms against 0.208;
+    // 14x14 over 4: 1,764, 0.187 against 0.190; batch 16 of it 2.38 against
+    // 2.64).  64 positions do not fit the registers (388 bytes of scratch).
     L->flat = 0;
-    if (p->stride == 1 && L->kh == 3 && L->kw == 3 && ck == 64 && L->ncc > 1 && L->cols <= 8 && L->xt == 16) {
+    if (p->stride == 1 && L->kh == 3 && L->kw == 3 && ck == 64 && L->ncc > 1 && L->wp <= 38) {
+        const uint64_t q = static_cast<uint64_t>(L->rows) * L->wp;
+        uint32_t pairs = 0;
+        for (uint32_t i = 0; i < p->k; ++i) pairs += label_words(p->moduli[i]);
         L->flat = 1;
-        L->xw = 16 + 2 * L->wp + 2;
+        L->xt = q > 16 && L->nimg * ((q + 31) / 32) * L->ogroups * pairs >= 1536 ? 32 : 16;
+        L->xw = L->xt + 2 * L->wp + 2;
         L->halo = L->xw * L->xstride;
         L->tile_rows = 1;
-        if (L->xw * (ck / 16) > 2 * kLinBlock) return REDASH_E_PARAM;  // not reached: wp <= 10
+        if (L->xw * (ck / 16) > 2 * kLinBlock) return REDASH_E_PARAM;  // not reached: at most 110 columns
     }
     L->ostride = L->xt + 4;  // the four lane groups of an atomic OR fall 16 banks apart
     L->lds_b = 4 * L->halo;
@@ -281,7 +290,7 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     // then the accumulator seeds of the 64 output channels (base, -b mod m)
     L->lds_bytes = L->lds_a + (L->lds_b > L->lds_o ? L->lds_b : L->lds_o) + 2 * kLinOTile * 4;
     if (L->lds_bytes > kLinMaxLds) return REDASH_E_PARAM;
-    L->xtiles = L->flat ? (L->rows * L->wp + 15) / 16 : (L->cols + L->xt - 1) / L->xt;
+    L->xtiles = (L->flat ? L->rows * L->wp + L->xt - 1 : L->cols + L->xt - 1) / L->xt;
     L->plane_bytes = static_cast<uint64_t>(L->nimg) * L->hp * L->wp * L->cp;
     // folded: a window's last piece may be read past the last position
     if (L->fold_c) L->plane_bytes = (L->plane_bytes + 64 + 63) / 64 * 64;
@@ -338,6 +347,14 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     const uint64_t tiles = static_cast<uint64_t>(L->nimg) * L->tile_rows * L->xtiles;
     const uint64_t grid_mod = (L->ncc > 1 ? tiles : (tiles + 3) / 4) * L->k * L->ogroups;  // 4 tiles per workgroup
     L->word_split = grid_mod < 2048 ? 1u : 0u;
+    // With a workgroup per word on flattened tiles, every workgroup of one
+    // modulus and output channel group reads the same weights (37 KB a chunk)
+    // once per group of four residues: the groups are dealt to the XCDs so that
+    // one L2 serves them (8 groups: one each; 4, 2 or 1: each group's words
+    // alternate between 2, 4 or 8 XCDs): 7x7 512 -> 512 0.208 -> 0.203 ms, 14x14
+    // 256 -> 256 0.187 -> 0.179.  Row tiles (stride 2) lose 1-2% by it: their
+    // neighbours share plane rows instead.
+    L->og_xcd = L->word_split && L->flat && (L->ogroups % kXcds == 0 || kXcds % L->ogroups == 0) ? 1u : 0u;
     L->total_planes = pl_off;
     L->rowsum_off = static_cast<uint64_t>(L->k) * L->ncc * L->o_pad * L->kc;
     return REDASH_OK;
@@ -618,17 +635,33 @@ k_linear_gemm(const LinPlan L, const uint8_t *__restrict__ planes, const uint8_t
     // consecutive tiles (neighbouring output rows, which share input rows) on
     // one XCD, whose L2 then serves the shared plane rows
     const uint32_t nb = gridDim.x, full = nb / kXcds * kXcds;
-    const uint32_t tile = blockIdx.x < full ? (blockIdx.x % kXcds) * (nb / kXcds) + blockIdx.x / kXcds : blockIdx.x;
+    uint32_t tile = blockIdx.x < full ? (blockIdx.x % kXcds) * (nb / kXcds) + blockIdx.x / kXcds : blockIdx.x;
     // one packed word (pair table entry blockIdx.z, the output channel group
     // blockIdx.y: the words of the small moduli, with the most residues, are
     // dispatched first for every group) or every word of modulus blockIdx.y
-    const uint32_t i = L.word_split ? L.pair_mod[blockIdx.z] : blockIdx.y;
-    const uint32_t og = L.word_split ? blockIdx.y : blockIdx.z;
+    uint32_t pair = blockIdx.z, og = L.word_split ? blockIdx.y : blockIdx.z;
+    if (L.og_xcd) {
+        // workgroup 8 s + x runs on XCD x: its s-th (word, tile)
+        const uint32_t x = blockIdx.x % kXcds, sl = blockIdx.x / kXcds;
+        const uint32_t tiles = L.nimg * L.tile_rows * L.xtiles, t = sl / tiles;
+        tile = sl - t * tiles;
+        if (L.ogroups >= kXcds) {
+            const uint32_t per = L.ogroups / kXcds;
+            pair = t / per;
+            og = x + kXcds * (t - pair * per);
+        } else {
+            const uint32_t share = kXcds / L.ogroups;
+            og = x / share;
+            pair = x % share + share * t;
+        }
+        if (pair >= L.npairs) return;  // (the whole workgroup, before any barrier)
+    }
+    const uint32_t i = L.word_split ? L.pair_mod[pair] : blockIdx.y;
     const uint32_t xtile = tile % L.xtiles;
     const uint32_t row = (tile / L.xtiles) % L.tile_rows;
     const uint32_t img = tile / (L.xtiles * L.tile_rows);
     const LinMod M = L.mod[i];
-    const uint32_t w_lo = L.word_split ? L.pair_word[blockIdx.z] : 0u;
+    const uint32_t w_lo = L.word_split ? L.pair_word[pair] : 0u;
     const uint32_t w_hi = L.word_split ? w_lo + 1 : M.W;
     constexpr uint32_t XT = 16 * NCB;
     const uint32_t x0 = xtile * XT;
@@ -1210,8 +1243,14 @@ int launch_gemm(const LinPlan &L, const uint8_t *planes, const uint8_t *prep, co
     if (rc) return rc;
     const uint64_t tiles = static_cast<uint64_t>(L.nimg) * L.tile_rows * L.xtiles;
     if (tiles >= (1ull << 31)) return REDASH_E_PARAM;
+    dim3 grid;
+    if (L.og_xcd) {
+        const uint64_t words = L.ogroups >= kXcds ? static_cast<uint64_t>(L.ogroups / kXcds) * L.npairs
+                                                  : (L.npairs + kXcds / L.ogroups - 1) / (kXcds / L.ogroups);
+        grid = dim3(static_cast<uint32_t>(kXcds * words * tiles));  // word_split: few
+    }
     hipLaunchKernelGGL((k_linear_gemm<NCB, GARBLE, K33>),
-                       L.word_split ? dim3(static_cast<uint32_t>(tiles), L.ogroups, L.npairs)
+                       L.og_xcd ? grid : L.word_split ? dim3(static_cast<uint32_t>(tiles), L.ogroups, L.npairs)
                                     : dim3(static_cast<uint32_t>(tiles), L.k, L.ogroups),
                        dim3(kLinBlock), L.lds_bytes, stream, L, planes, prep, bias, offsets, out);
     return lin_launched();

@@ -70,7 +70,19 @@ SMALL = [
     # flattened tiles (3x3 stride 1 over several chunks, rows of at most 8 outputs)
     ("flat-narrow-batch2-ragged", (2, 3, 5, 7, 37), (2, 128, 5, 6), 70, 3, 3, 1, 1),
     ("flat-narrow-nopad-m251", (3, 5, 251), (1, 130, 9, 10), 9, 3, 3, 1, 0),
+    # flattened 32-position tiles, output channel groups dealt to the XCDs
+    # (1, 2, 4, 8 and 16 groups; 3 are not), ragged last tiles, up to 38 plane columns
+    ("flat-32-one-group", (223, 227, 229, 233, 239, 241, 251), (2, 65, 20, 34), 3, 3, 3, 1, 1),
+    ("flat-32-36-columns", (223, 227, 229, 233, 239, 241, 251), (4, 65, 9, 36), 2, 3, 3, 1, 1),
+    ("flat-two-groups", (2, 3, 5, 7, 11, 13), (1, 65, 4, 5), 128, 3, 3, 1, 1),
+    ("flat-three-groups", (2, 37), (1, 70, 3, 5), 190, 3, 3, 1, 1),
+    ("flat-four-groups", (3, 8, 13), (1, 65, 3, 5), 250, 3, 3, 1, 1),
+    ("flat-eight-groups", (2, 251), (1, 65, 3, 4), 510, 3, 3, 1, 1),
+    ("flat-sixteen-groups", (5,), (1, 66, 3, 4), 1000, 3, 3, 1, 1),
+    ("no-flat-39-plane-columns", (5, 7), (1, 65, 3, 37), 4, 3, 3, 1, 1),
     # column fold (fewer than 16 channels, kw c_in <= 64: kh x 1 over kw c_in channels)
+    ("fold-48-channels-stride4-rows", (3, 16, 251), (1, 12, 9, 18), 70, 3, 4, 4, 0),
+    ("fold-32-rows-16-channels", (2, 3), (1, 8, 40, 9), 3, 32, 2, 1, 0),
     ("fold-63-channels-m251", (2, 251), (1, 9, 11, 13), 5, 7, 7, 1, 3),
     ("no-fold-63-channels-stride2-halo", (2, 251), (1, 9, 11, 13), 5, 7, 7, 2, 3),
     ("fold-one-channel-5x5", (3, 5, 7, 11), (2, 1, 9, 23), 4, 5, 5, 1, 2),
