@@ -222,7 +222,7 @@ __device__ __forceinline__ PermTE02 perm_te02() {
 // several waves of a SIMD have an instruction ready, one in its AES rounds
 // (which keep the LDS pipe busy with table reads) issues before one in other
 // work (mostly VALU), so the two pipes stay busy together.
-template <int NB, bool PAIRED = false, typename Tab, typename Key>
+template <int NB, typename Tab, typename Key>
 __device__ __forceinline__ void aes128_encrypt_n(const Tab &T, uint32_t (&s)[NB][4], const Key &K) {
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
@@ -230,21 +230,7 @@ __device__ __forceinline__ void aes128_encrypt_n(const Tab &T, uint32_t (&s)[NB]
 #pragma unroll
         for (int c = 0; c < 4; ++c) s[b][c] ^= K(c);
     // Rounds 1..9 stay a loop (the round keys are uniform loads): the
-    // instruction cache holds the whole gate loop that way.  A round's new
-    // state needs registers of its own while the old one is read, so a loop
-    // of one round per pass copies the state back at the end of every pass.
-    // PAIRED takes two rounds per pass, the state going to t and back to s,
-    // without the copies; it holds more values live, which pays only where
-    // the kernel has registers to spare.
-    auto round_to = [&](const uint32_t(&in)[NB][4], uint32_t(&o)[NB][4], int r) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            o[b][0] = T.column(in[b][0], in[b][1], in[b][2], in[b][3], K, 4 * r);
-            o[b][1] = T.column(in[b][1], in[b][2], in[b][3], in[b][0], K, 4 * r + 1);
-            o[b][2] = T.column(in[b][2], in[b][3], in[b][0], in[b][1], K, 4 * r + 2);
-            o[b][3] = T.column(in[b][3], in[b][0], in[b][1], in[b][2], K, 4 * r + 3);
-        }
-    };
+    // instruction cache holds the whole gate loop that way.
     auto last_round = [&](const uint32_t(&in)[NB][4]) {
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
@@ -255,29 +241,18 @@ __device__ __forceinline__ void aes128_encrypt_n(const Tab &T, uint32_t (&s)[NB]
             s[b][3] = T.last_column(s3, s0, s1, s2, K, 43);
         }
     };
-    if constexpr (PAIRED) {
-        uint32_t t[NB][4];
 #pragma unroll 1
-        for (int r = 1; r < 9; r += 2) {
-            round_to(s, t, r);
-            round_to(t, s, r + 1);
-        }
-        round_to(s, t, 9);
-        last_round(t);
-    } else {
-#pragma unroll 1
-        for (int r = 1; r < 10; ++r) {
+    for (int r = 1; r < 10; ++r) {
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const uint32_t s0 = s[b][0], s1 = s[b][1], s2 = s[b][2], s3 = s[b][3];
-                s[b][0] = T.column(s0, s1, s2, s3, K, 4 * r);
-                s[b][1] = T.column(s1, s2, s3, s0, K, 4 * r + 1);
-                s[b][2] = T.column(s2, s3, s0, s1, K, 4 * r + 2);
-                s[b][3] = T.column(s3, s0, s1, s2, K, 4 * r + 3);
-            }
+        for (int b = 0; b < NB; ++b) {
+            const uint32_t s0 = s[b][0], s1 = s[b][1], s2 = s[b][2], s3 = s[b][3];
+            s[b][0] = T.column(s0, s1, s2, s3, K, 4 * r);
+            s[b][1] = T.column(s1, s2, s3, s0, K, 4 * r + 1);
+            s[b][2] = T.column(s2, s3, s0, s1, K, 4 * r + 2);
+            s[b][3] = T.column(s3, s0, s1, s2, K, 4 * r + 3);
         }
-        last_round(s);
     }
+    last_round(s);
     __builtin_amdgcn_s_setprio(0);
 }
 
@@ -696,14 +671,6 @@ __device__ __forceinline__ uint32_t swar_add(uint32_t x, uint32_t ue, uint32_t u
 // (x - u) mod m in every field (m > 2): x + (m - u), km = m in every even field.
 __device__ __forceinline__ uint32_t swar_sub(uint32_t x, uint32_t u, uint32_t km, const ModConst &mc) {
     return swar_add(x, km - (u & mc.sw_even), km - ((u >> mc.b) & mc.sw_even), mc);
-}
-
-// (x + u) mod m residue by residue for one packed word (any m; m = 2 is XOR).
-__device__ __forceinline__ uint32_t word_add(uint32_t x, uint32_t u, uint32_t nres, const ModConst &mc) {
-    if (mc.m == 2) return x ^ u;
-    uint32_t out = 0;
-    for (uint32_t j = 0; j < nres; ++j) out |= add_mod(field(x, j, mc), field(u, j, mc), mc.m) << (mc.b * j);
-    return out;
 }
 
 // For m = 2 (128-bit fraction in V[0..3]) digit r is bit 127 - r of V, so
