@@ -962,21 +962,16 @@ __device__ __forceinline__ uint32_t mod64(int64_t x, uint32_t m) {
     return r;
 }
 
-// The index of this workgroup's 64 gadgets (grid_of_64: rows of 2^18, so that
-// no dimension reaches 2^32 work-items at 15 waves a workgroup).
-__device__ __forceinline__ uint64_t group64() {
-    return static_cast<uint64_t>(blockIdx.y) * (1u << 18) + blockIdx.x;
-}
-
-// A workgroup takes 64 gadgets and one wave per modulus (at most 15): the
-// modulus stays uniform in a wave and a small call still fills waves (65,536
-// gadgets over 10 primes: 49 us with every modulus of a gadget on one lane).
-// P is a multiple of m_i: (x mod P) mod m_i = x mod m_i.
-__global__ void __launch_bounds__(64 * kMaxK) k_encode(const Plan P, const int64_t *__restrict__ x,
-                                                       const uint32_t *__restrict__ zero,
-                                                       const uint32_t *__restrict__ offsets, uint32_t *__restrict__ lab) {
-    const uint32_t i = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    const uint64_t a = group64() * 64 + threadIdx.x % 64;
+// A workgroup takes 256 gadgets and one modulus (blockIdx.y): the modulus is
+// uniform, a small call still fills waves (65,536 gadgets over 10 primes: 49 us
+// with every modulus of a gadget on one lane), and a large one streams whole
+// kilobytes of each word.  P is a multiple of m_i: (x mod P) mod m_i = x mod m_i.
+template <int BLOCK>
+__global__ void __launch_bounds__(BLOCK) k_encode(const Plan P, const int64_t *__restrict__ x,
+                                                  const uint32_t *__restrict__ zero,
+                                                  const uint32_t *__restrict__ offsets, uint32_t *__restrict__ lab) {
+    const uint32_t i = blockIdx.y;
+    const uint64_t a = static_cast<uint64_t>(blockIdx.x) * BLOCK + threadIdx.x;
     if (a >= P.n) return;
     const uint64_t n = P.n;
     const ModConst mc = P.mod[i];
@@ -995,20 +990,26 @@ struct CrtConst {
     uint64_t quot[kMaxK];  // P / m_i
     uint32_t inv[kMaxK];   // c_i
 };
-static_assert(sizeof(Plan) + sizeof(CrtConst) + 5 * sizeof(void *) <= 4096, "decode's arguments fit the argument block");
+static_assert(sizeof(Plan) + sizeof(CrtConst) + 6 * sizeof(void *) <= 4096, "decode's arguments fit the argument block");
 
-// Workgroups as k_encode's: wave i checks the labels over modulus i and finds
-// their value; then one wave sums the CRT terms of its 64 gadgets (every
-// partial sum reduced below P < 2^63) and counts the bad ones.
-__global__ void __launch_bounds__(64 * kMaxK) k_decode(const Plan P, const CrtConst C, const uint32_t *__restrict__ Y,
-                                                       const uint32_t *__restrict__ O,
-                                                       const uint32_t *__restrict__ offsets, int64_t *__restrict__ y,
-                                                       unsigned long long *__restrict__ bad) {
-    __shared__ uint32_t term[kMaxK * 64];  // v_i c_i mod m_i, bit 31: the label is not O + v R
-    const uint32_t i = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
-    const uint64_t a = group64() * 64 + lane;
+// A workgroup takes 64 G gadgets with S waves per 64: wave (part, grp) checks
+// the labels over moduli part, part + S, ... of group grp and finds their
+// values; then the waves of part 0 sum the CRT terms of their gadgets (every
+// partial sum reduced below P < 2^63) and count the bad ones.  G = 1, S = k
+// for small calls (a wave per modulus), G = S = 4 for large ones, whose
+// workgroups then read whole kilobytes of each word.
+__global__ void __launch_bounds__(1024) k_decode(const Plan P, const CrtConst C, const uint32_t *__restrict__ Y,
+                                                 const uint32_t *__restrict__ O, const uint32_t *__restrict__ offsets,
+                                                 int64_t *__restrict__ y, unsigned long long *__restrict__ bad,
+                                                 uint32_t G, uint32_t S) {
+    __shared__ uint32_t terms[kMaxK * 256];  // v_i c_i mod m_i, bit 31: the label is not O + v R
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
+    const uint32_t grp = wave % G, part = wave / G;
+    uint32_t *term = terms + grp * (kMaxK * 64);
+    const uint64_t a = (static_cast<uint64_t>(blockIdx.x) * G + grp) * 64 + lane;
     const uint64_t n = P.n;
-    if (a < n) {
+    for (uint32_t i = part; i < P.k; i += S) {
+        if (a >= n) continue;  // (a lane's choice: the loop itself stays uniform)
         const ModConst mc = P.mod[i];
         const uint64_t base = static_cast<uint64_t>(mc.woff) * n + a;
         const uint32_t y0 = Y[base] & mc.mask, o0 = O[base] & mc.mask;
@@ -1022,7 +1023,7 @@ __global__ void __launch_bounds__(64 * kMaxK) k_decode(const Plan P, const CrtCo
         term[i * 64 + lane] = ((vi % mc.m) * C.inv[i]) % mc.m | (ok ? 0u : 0x80000000u);
     }
     __syncthreads();
-    if (i != 0 || a >= n) return;
+    if (part != 0 || a >= n) return;
     uint64_t val = 0;
     uint32_t flags = 0;
     for (uint32_t j = 0; j < P.k; ++j) {
@@ -1185,13 +1186,6 @@ int allow_lds(const void *kernel, size_t bytes) {
                    hipSuccess
                ? REDASH_OK
                : REDASH_E_HIP;
-}
-
-// One workgroup per 64 gadgets, in rows of at most 2^18 (see group64).
-dim3 grid_of_64(uint64_t n) {
-    const uint64_t groups = (n + 63) / 64, row = 1u << 18;
-    return groups <= row ? dim3(static_cast<unsigned>(groups))
-                         : dim3(static_cast<unsigned>(row), static_cast<unsigned>((groups + row - 1) / row));
 }
 
 unsigned grid_for(uint64_t n, int block) { return static_cast<unsigned>((n + block - 1) / block); }
@@ -1393,7 +1387,7 @@ int redash_encode(const redash_params *p, const int64_t *d_x, const uint32_t *d_
     if (!d_offsets) return REDASH_E_NULL;
     if (P.n == 0) return REDASH_OK;
     if (!d_x || !d_in_zero || !d_in_labels) return REDASH_E_NULL;
-    hipLaunchKernelGGL(k_encode, grid_of_64(P.n), dim3(64 * P.k), 0, stream, P, d_x, d_in_zero, d_offsets,
+    hipLaunchKernelGGL(k_encode<256>, dim3(grid_for(P.n, 256), P.k), dim3(256), 0, stream, P, d_x, d_in_zero, d_offsets,
                        d_in_labels);
     return launched();
 }
@@ -1483,8 +1477,10 @@ int redash_decode(const redash_params *p, const uint32_t *d_out_labels, const ui
         C.quot[i] = P.P / P.mod[i].m;
         C.inv[i] = inverse_mod(static_cast<uint32_t>(C.quot[i] % P.mod[i].m), P.mod[i].m);
     }
-    hipLaunchKernelGGL(k_decode, grid_of_64(P.n), dim3(64 * P.k), 0, stream, P, C, d_out_labels, d_out_zero,
-                       d_offsets, d_y, bad);
+    const bool wide = P.n > (1u << 18);
+    const uint32_t G = wide ? 4u : 1u, S = wide ? 4u : P.k;
+    hipLaunchKernelGGL(k_decode, dim3(grid_for(P.n, static_cast<int>(64 * G))), dim3(64 * G * S), 0, stream, P, C,
+                       d_out_labels, d_out_zero, d_offsets, d_y, bad, G, S);
     return launched();
 }
 
