@@ -15,10 +15,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libredash.so")
 SOURCES = [os.path.join(CSRC, "redash.hip"), os.path.join(CSRC, "linear.hip"), os.path.join(CSRC, "aes_rate.hip"),
-           os.path.join(CSRC, "plan.cpp")]
-HEADERS = [os.path.join(CSRC, f) for f in ("aes_tables.hpp", "aes_bitslice.hpp", "device.hpp", "plan.hpp")] + [
-    os.path.join(ROOT, "include", "redash.h")
-]
+           os.path.join(CSRC, "plan.cpp"), os.path.join(CSRC, "linear_plan.cpp")]
+HEADERS = [os.path.join(CSRC, f) for f in ("aes_tables.hpp", "aes_bitslice.hpp", "device.hpp", "plan.hpp",
+                                            "linear_plan.hpp")] + [os.path.join(ROOT, "include", "redash.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

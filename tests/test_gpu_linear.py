@@ -25,6 +25,7 @@ from paper_2506_14489_amd import binding as B  # noqa: E402
 from paper_2506_14489_amd import workloads as WL  # noqa: E402
 
 import gpu_helpers as H  # noqa: E402
+import linear_cases as LC  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -290,12 +291,13 @@ def test_full_size_resnet18_layer(layer):
     _check_full_layer(layer, 24)
 
 
-def test_full_size_several_chunks_one_workgroup_per_modulus():
-    """Two images of ResNet-18's 128-channel 28x28 layer: a grid large enough
-    (2,688 workgroups) that the several-chunk contraction gives each modulus
-    one workgroup; the batch-1 layers above give each packed word one."""
-    w = WL._conv("l2.b-batch2", WL.PRIMES_12, (11,), 31, (2, 128, 28, 28), 128, 3, 1, 1)
-    _check_full_layer(w, 24)
+@pytest.mark.parametrize("layer", [w for w, _plan in LC.SEVERAL_CHUNKS], ids=lambda w: w.name)
+def test_full_size_several_chunks(layer):
+    """3x3 layers over several channel chunks on the launch shapes that the
+    batch-1 layers above do not take, the grid of one workgroup per modulus
+    among them (linear_cases.py names each one's; test_linear_plan.py checks
+    on the CPU that the layer takes it)."""
+    _check_full_layer(layer, 24)
 
 
 # ---------------------------------------------------------------------------
