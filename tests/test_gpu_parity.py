@@ -22,6 +22,7 @@ from paper_2506_14489_amd import binding as B  # noqa: E402
 from paper_2506_14489_amd import workloads as WL  # noqa: E402
 
 import gpu_helpers as H  # noqa: E402
+from pad_cases import PAD_CASES  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -647,6 +648,44 @@ def test_small_calls(name, moduli, S, per_cu, extra):
     w = WL.Workload(f"small-{name}", tuple(moduli), tuple(S), n, 120 + per_cu + extra, "uniform", -(P // 2),
                     P - P // 2)
     _check_full(w, 2048, 2048, 2048, 4)
+
+
+# Pads whose leading limbs alone give wrong digits (pad_cases.py): garbler and
+# evaluator would agree on a wrong pad and decode it, so the gadgets are
+# compared with the oracle word for word: table rows, zero-labels and output
+# labels.  (name, gadgets per CU): a lane per gate and gadget, the splits, one
+# gadget per lane; the garbler takes 8, 4 and 1 waves per 64 gadgets there.
+PAD_SIZES = [("small", 0), ("split12", 24), ("split4", 200), ("lane", 832)]
+
+
+@pytest.mark.parametrize("size,per_cu", PAD_SIZES, ids=[s[0] for s in PAD_SIZES])
+@pytest.mark.parametrize("name", PAD_CASES)
+def test_pads_that_need_all_limbs(name, size, per_cu):
+    moduli, S, seed, hits = PAD_CASES[name]
+    n = torch.cuda.get_device_properties(0).multi_processor_count * per_cu + 33
+    op = O.make_params(list(moduli), list(S), 1, seed)
+    gq = H.gate_list_sizes(O.gate_list(op), moduli)
+    hits = sorted(hits)
+    while hits:
+        a0 = max(hits[0][0] - 7, 0)
+        here = [h for h in hits if h[0] < a0 + n]
+        hits = hits[len(here):]
+        x = np.zeros(n, np.int64)
+        for a, _g, v in here:
+            x[a - a0] = v
+        print(f"pads {name} {size}: a0={a0} n={n} gadgets {[h[:2] for h in here]}", flush=True)
+        buf = H.gpu_pipeline(B.make_params(moduli, S, n, seed, a0), x)
+        for a, g, v in here:
+            at = np.array([a - a0], dtype=np.int64)
+            offs, zin, zout, tab = O.garble(op, a, 1)
+            Y = O.evaluate(op, a, 1, O.encode(op, np.array([v]), zin, offs), tab)
+            li = H.label_index(moduli, n, at)
+            assert np.array_equal(H.gather(buf.out_zero, li), zout), (a, g)
+            assert np.array_equal(H.gather(buf.tables, H.table_index(gq, n, at)), tab), (a, g)
+            assert np.array_equal(H.gather(buf.out_labels, li), Y), (a, g)
+        assert int(buf.bad.item()) == 0
+        del buf
+        torch.cuda.empty_cache()
 
 
 # The garbler gives 64 gadgets 8, 4, 2 or 1 waves, as many as one round of two
