@@ -115,7 +115,9 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     L->ncc = (L->c_in + ck - 1) / ck;
     L->cp = L->fold_c ? L->fold_c : L->ncc * ck;
     L->hp = L->in_rows + 2 * p->pad;
-    L->wp = L->in_cols + 2 * p->pad;
+    // (folded: up to the last window's end, so that a plane never takes more
+    // than ck bytes for each column a window can begin at)
+    L->wp = L->fold_c ? (L->cols - 1) * p->stride + p->kw : L->in_cols + 2 * p->pad;
     L->gstep = L->fold_c ? p->stride : 1;
     L->lstep = L->fold_c ? 1 : p->stride;
     L->xlast = L->fold_c ? (L->cols - 1) * p->stride : L->wp - 1;
@@ -198,8 +200,9 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     if (L->lds_bytes > kLinMaxLds) return REDASH_E_PARAM;
     L->xtiles = (L->flat ? L->rows * L->wp + L->xt - 1 : L->cols + L->xt - 1) / L->xt;
     L->plane_bytes = static_cast<uint64_t>(L->nimg) * L->hp * L->wp * L->cp;
-    // folded: a window's last piece may be read past the last position
-    if (L->fold_c) L->plane_bytes = (L->plane_bytes + 64 + 63) / 64 * 64;
+    // folded: the last window's pieces are read past the last position (c_in
+    // is kw times the layer's own), and whole words are written
+    if (L->fold_c) L->plane_bytes = (L->plane_bytes + (ck - L->c_in) + 15) / 16 * 16;
     if (L->plane_bytes >= (1ull << 32)) return REDASH_E_PARAM;  // 32-bit offsets within a plane
 
     uint32_t woff = 0, pl_off = 0, np = 0;
