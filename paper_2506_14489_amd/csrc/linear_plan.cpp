@@ -18,6 +18,101 @@ uint32_t gcd32(uint32_t a, uint32_t b) {
 
 uint32_t round_up(uint32_t v, uint32_t q) { return (v + q - 1) / q * q; }
 
+// The forms of a 3x3 stride-1 layer over several 64-channel chunks: 16-position
+// tiles of a row, or 16- or 32-position tiles of the flattened plane, each with
+// a workgroup per modulus or per packed word.
+//
+// Estimated time of one (us, up to a part that is the same for all): a stage
+// (four residues of a word, one chunk) on each of the 512 workgroups that run
+// together costs `stage` and `column` for each 100 staged columns, a workgroup
+// `start`, the stages of the longest workgroup `serial` each (the launch ends
+// with such a one), the launch `fixed`.  Fitted to the times of 700 layers (65 to
+// 512 channels, 16 to 512 outputs, 4 to 36 columns, batch 1 to 16, four bases;
+// relative error 6-11%).  Over them the form chosen is on geometric mean 0.6%
+// slower than the fastest of the six, and over 150 others 15% faster than row
+// tiles for more than 8 columns and 7% faster than flattened tiles everywhere,
+// which cost rows of 16 or 32 positions and small or unevenly filled grids up to
+// 40% (128 -> 128 channels at 16x16 71 us in rows, 82 flattened; 8 primes, 192 ->
+// 64 at 32x32 138 and 191; 512 -> 512 at 8x8, batch 8, 2.07 ms at 16 positions,
+// 2.81 at 32, 1.78 at 16 with a workgroup per word).
+struct FormCost {
+    double stage, column, serial, start, fixed;
+};
+constexpr FormCost kFormCost[3][2] = {
+    // {a workgroup per modulus, per word}
+    {{1.93, 0, 1.1, 7.4, 14}, {2.07, 0, 0.73, 3.2, 11}},        // tiles of a row
+    {{1.49, 0.74, 1.2, 6.6, 14.5}, {1.56, 0.89, 0.92, 3.0, 11.5}},  // flattened, 16 positions
+    {{2.93, 0.64, 2.6, 0, 20.5}, {2.49, 1.5, 1.95, 2.9, 13}},   // flattened, 32 positions
+};
+constexpr int kRowTiles = 0, kFlat16 = 1, kFlat32 = 2;
+
+struct Form {
+    int tiles;
+    bool split;  // a workgroup per packed word
+};
+
+// With a workgroup per word on flattened tiles, every workgroup of one modulus
+// and output channel group reads the same weights (37 KB a chunk) once per group
+// of four residues.  Where the layer's weights (36 KB per modulus, chunk and
+// group) exceed what an XCD's 4 MB L2 holds of them beside the planes, the groups
+// are dealt to the XCDs so that one L2 serves a group.  32-position tiles wait for
+// their weights and gain 4% on geometric mean from 7 MB on (49 of the 700 layers;
+// 14x14 256 -> 256 189 -> 178 us, 512 -> 512 15%), and lose as much where the
+// weights are few; 16-position tiles hold the next chunk's weights in registers
+// and gain 2-3% on layers of few tiles with 8 groups (7x7 512 -> 512 208 -> 203
+// us), else lose: a word's workgroups then no longer share plane lines in one L2
+// (2 or 4 groups 2-3%, one group 17%).
+bool deal_groups(int tiles, uint32_t k, uint32_t ncc, uint32_t ogroups) {
+    const uint32_t weights = k * ncc * ogroups;  // in 36 KB
+    if (tiles == kFlat16) return ogroups % kXcds == 0 && weights >= 384;
+    return tiles == kFlat32 && (ogroups % kXcds == 0 || ogroups == 2 || ogroups == 4) && weights >= 192;
+}
+
+uint64_t form_tiles(const LinPlan &L, int tiles) {
+    const uint64_t q = static_cast<uint64_t>(L.rows) * L.wp;
+    return L.nimg * (tiles == kRowTiles ? static_cast<uint64_t>(L.rows) * ((L.cols + 15) / 16)
+                     : tiles == kFlat16 ? (q + 15) / 16
+                                        : (q + 31) / 32);
+}
+
+// L: rows, cols, wp, nimg, ncc and ogroups filled.
+Form choose_form(const LinPlan &L, const redash_linear_params *p) {
+    uint32_t pairs = 0, total = 0, most[2] = {0, 0};  // packed words, stages of a tile, of its longest workgroup
+    for (uint32_t i = 0; i < p->k; ++i) {
+        ModConst mc;
+        fill_mod_const(p->moduli[i], &mc);
+        const uint32_t full = (mc.g + 3) / 4, last = (mc.glast + 3) / 4, all = (mc.W - 1) * full + last;
+        pairs += mc.W;
+        total += all;
+        if (all > most[0]) most[0] = all;
+        if (full > most[1]) most[1] = full;
+    }
+    auto cost = [&](const Form &f) -> double {
+        const FormCost &c = kFormCost[f.tiles][f.split];
+        const double groups = static_cast<double>(form_tiles(L, f.tiles)) * L.ogroups;
+        const double columns = f.tiles == kRowTiles ? 0 : (f.tiles == kFlat16 ? 16 : 32) + 2.0 * L.wp + 2;
+        const double stages = groups * total * L.ncc, workgroups = groups * (f.split ? pairs : p->k);
+        const double t = (stages * (c.stage + c.column * columns / 100) + workgroups * c.start) / 512 +
+                         c.serial * most[f.split] * L.ncc + c.fixed;
+        return f.split && deal_groups(f.tiles, p->k, L.ncc, L.ogroups) ? 0.95 * t : t;
+    };
+    // the simplest form unless another promises 2%: rows of at most 8 outputs
+    // flattened, wider ones in row tiles
+    Form best;
+    best.tiles = L.cols <= 8 ? kFlat16 : kRowTiles;
+    best.split = form_tiles(L, best.tiles) * p->k * L.ogroups < 2048;
+    double least = cost(best) / 1.02;
+    for (int tiles : {kRowTiles, kFlat16, kFlat32})
+        for (bool split : {false, true}) {
+            const double t = cost(Form{tiles, split});
+            if (t < least) {
+                least = t;
+                best = Form{tiles, split};
+            }
+        }
+    return best;
+}
+
 }  // namespace
 
 int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
@@ -174,17 +269,15 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     // the store.  Rows narrower than a tile leave no matrix columns idle that
     // way, and the staged run of a 32-position tile fits two workgroups per CU
     // up to 38 plane columns: a stage's weights (36 KB for four residues and a
-    // chunk) then serve twice the positions.  16 where 32 would leave too few
-    // workgroups (7x7 over 8 groups of outputs: 1,008, 0.268 ms against 0.208;
-    // 14x14 over 4: 1,764, 0.187 against 0.190; batch 16 of it 2.38 against
-    // 2.64).  64 positions do not fit the registers (388 bytes of scratch).
+    // chunk) then serve twice the positions.  (64 positions do not fit the
+    // registers: 388 bytes of scratch.)  Which form: choose_form.
     L->flat = 0;
-    if (p->stride == 1 && L->kh == 3 && L->kw == 3 && ck == 64 && L->ncc > 1 && L->wp <= 38) {
-        const uint64_t q = static_cast<uint64_t>(L->rows) * L->wp;
-        uint32_t pairs = 0;
-        for (uint32_t i = 0; i < p->k; ++i) pairs += label_words(p->moduli[i]);
+    const bool several33 = p->stride == 1 && L->kh == 3 && L->kw == 3 && ck == 64 && L->ncc > 1 && L->wp <= 38;
+    Form form{kRowTiles, false};
+    if (several33) form = choose_form(*L, p);
+    if (form.tiles != kRowTiles) {
         L->flat = 1;
-        L->xt = q > 16 && L->nimg * ((q + 31) / 32) * L->ogroups * pairs >= 1536 ? 32 : 16;
+        L->xt = form.tiles == kFlat32 ? 32 : 16;
         L->xw = L->xt + 2 * L->wp + 2;
         L->halo = L->xw * L->xstride;
         L->tile_rows = 1;
@@ -255,15 +348,9 @@ int build_lin_plan(const redash_linear_params *p, LinPlan *L) {
     // where the chip is full either way.
     const uint64_t tiles = static_cast<uint64_t>(L->nimg) * L->tile_rows * L->xtiles;
     const uint64_t grid_mod = (L->ncc > 1 ? tiles : (tiles + 3) / 4) * L->k * L->ogroups;  // 4 tiles per workgroup
-    L->word_split = grid_mod < 2048 ? 1u : 0u;
-    // With a workgroup per word on flattened tiles, every workgroup of one
-    // modulus and output channel group reads the same weights (37 KB a chunk)
-    // once per group of four residues: the groups are dealt to the XCDs so that
-    // one L2 serves them (8 groups: one each; 4, 2 or 1: each group's words
-    // alternate between 2, 4 or 8 XCDs): 7x7 512 -> 512 0.208 -> 0.203 ms, 14x14
-    // 256 -> 256 0.187 -> 0.179.  Row tiles (stride 2) lose 1-2% by it: their
-    // neighbours share plane rows instead.
-    L->og_xcd = L->word_split && L->flat && (L->ogroups % kXcds == 0 || kXcds % L->ogroups == 0) ? 1u : 0u;
+    L->word_split = several33 ? form.split : grid_mod < 2048;
+    L->og_xcd = L->word_split && L->flat && deal_groups(form.tiles, L->k, L->ncc, L->ogroups) &&
+                tiles * L->npairs * L->ogroups < (1u << 28);  // (a one-dimensional grid, up to 7 words more)
     L->total_planes = pl_off;
     L->rowsum_off = static_cast<uint64_t>(L->k) * L->ncc * L->o_pad * L->kc;
     return REDASH_OK;

@@ -42,13 +42,13 @@ SMALL = [
     ("conv3x3-two-chunks-stride2", (3, 5, 7, 31), (1, 128, 14, 14), 70, 3, 3, 2, 1),
     # flattened tiles (3x3 stride 1 over several chunks)
     ("flat-narrow-batch2-ragged", (2, 3, 5, 7, 37), (2, 128, 5, 6), 70, 3, 3, 1, 1),
-    ("flat-narrow-nopad-m251", (3, 5, 251), (1, 130, 9, 10), 9, 3, 3, 1, 0),
-    # flattened 32-position tiles, output channel groups dealt to the XCDs
-    # (1, 2, 4, 8 and 16 groups; 3 are not), ragged last tiles, up to 38 plane columns
+    ("flat-narrow-nopad-m251", (3, 5, 251), (2, 130, 9, 8), 9, 3, 3, 1, 0),
+    # flattened 32-position tiles, ragged last tiles, up to 38 plane columns; 1 to
+    # 16 output channel groups
     ("flat-32-one-group", (223, 227, 229, 233, 239, 241, 251), (2, 65, 20, 34), 3, 3, 3, 1, 1),
     ("flat-32-36-columns", (223, 227, 229, 233, 239, 241, 251), (4, 65, 9, 36), 2, 3, 3, 1, 1),
     ("flat-two-groups", (2, 3, 5, 7, 11, 13), (1, 65, 4, 5), 128, 3, 3, 1, 1),
-    ("flat-three-groups", (2, 37), (1, 70, 3, 5), 190, 3, 3, 1, 1),
+    ("flat-three-groups", (2, 3, 37), (1, 70, 4, 5), 190, 3, 3, 1, 1),
     ("flat-four-groups", (3, 8, 13), (1, 65, 3, 5), 250, 3, 3, 1, 1),
     ("flat-eight-groups", (2, 251), (1, 65, 3, 4), 510, 3, 3, 1, 1),
     ("flat-sixteen-groups", (5,), (1, 66, 3, 4), 1000, 3, 3, 1, 1),
@@ -73,10 +73,24 @@ SMALL = [
 ]
 
 # 3x3 layers over several channel chunks at full size: (workload, what the
-# plan has to say).  word_split 0: each modulus has one workgroup per tile
-# and channel group, 1: each packed word has one.
+# plan has to say), one for each form of the kernel.  word_split 0: each modulus
+# has one workgroup per tile and channel group, 1: each packed word has one;
+# og_xcd 1: the channel groups are dealt to the XCDs.
+def _form(flat, xt, word_split, og_xcd=0):
+    return {"flat": flat, "xt": xt, "word_split": word_split, "og_xcd": og_xcd}
+
+
 SEVERAL_CHUNKS = [
-    (_conv("l2.b-batch4", 31, (4, 128, 28, 28), 128), {"ncc": 2, "flat": 1, "xt": 32, "word_split": 0, "og_xcd": 0}),
-    (_conv("row-tiles-56x56", 32, (1, 128, 56, 56), 64), {"ncc": 2, "flat": 0, "xt": 16, "word_split": 0, "og_xcd": 0}),
-    (_conv("stride2-batch8", 33, (8, 128, 28, 28), 256, 2), {"ncc": 2, "flat": 0, "xt": 16, "word_split": 0, "og_xcd": 0}),
+    (_conv("rows-modulus-39-columns", 32, (1, 128, 56, 56), 64), _form(0, 16, 0)),
+    (_conv("rows-modulus-stride2", 33, (8, 128, 28, 28), 256, 2), _form(0, 16, 0)),
+    (_conv("rows-modulus", 34, (2, 96, 32, 32), 96), _form(0, 16, 0)),
+    (_conv("rows-word", 35, (1, 128, 16, 16), 128), _form(0, 16, 1)),
+    (_conv("flat16-modulus", 36, (16, 96, 5, 5), 320), _form(1, 16, 0)),
+    (_conv("flat16-word", 37, (4, 128, 7, 7), 128), _form(1, 16, 1)),
+    (_conv("flat16-word-dealt-8", 38, (1, 256, 5, 5), 512), _form(1, 16, 1, 1)),
+    (_conv("flat32-modulus", 39, (4, 96, 30, 30), 96), _form(1, 32, 0)),
+    (_conv("flat32-word", 31, (2, 128, 28, 28), 128), _form(1, 32, 1)),
+    (_conv("flat32-word-dealt-2", 40, (1, 512, 20, 20), 96), _form(1, 32, 1, 1)),
+    (_conv("flat32-word-dealt-4", 41, (1, 256, 14, 14), 256), _form(1, 32, 1, 1)),
+    (_conv("flat32-word-dealt-8", 42, (2, 96, 7, 7), 512), _form(1, 32, 1, 1)),
 ]

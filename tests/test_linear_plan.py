@@ -49,6 +49,7 @@ def test_full_size_layers_take_their_paths(plan_of):
     got = plan_of([(w.moduli, w.in_shape, w.w_shape[0], w.w_shape[2], w.w_shape[3], w.stride, w.pad)
                    for w, _want in LC.SEVERAL_CHUNKS])
     for (w, want), plan in zip(LC.SEVERAL_CHUNKS, got):
+        assert plan["ncc"] > 1
         assert {k: plan.get(k) for k in want} == want, (w.name, plan)
 
 
