@@ -284,14 +284,19 @@ __device__ __forceinline__ v4i plane_field(const v4i &v, const LinMod &M, uint32
 // ---------------------------------------------------------------------------
 // The contraction.
 // ---------------------------------------------------------------------------
-// (At least two waves per SIMD; where the registers and the LDS allow three or
-// four, as without K33 on 16-position tiles, they run: 1x1 256 -> 512 stride 2
-// at 14x14 0.121 -> 0.094 ms.)
+// At least two waves per SIMD; without K33, on 16-position tiles, the registers
+// and the LDS allow three (1x1 256 -> 512 stride 2 at 14x14 0.121 -> 0.094 ms).
+// With K33 only two fit, and the upper bound lets the compiler schedule for two
+// (3x3 stride 2 256 -> 512 at 14x14 202 -> 198.5 us, on a short base batch 8
+// 197.5 -> 194.0).
 // K33 (> 0): a 3x3 kernel with 64-channel chunks (taps = K steps, kc = 576)
 // and K33 bytes per staged column, the K loop unrolled with every fragment
-// offset known but the row stride; 0: any kernel.
-template <int NCB, bool GARBLE, int K33>
-__global__ void __launch_bounds__(kLinBlock) __attribute__((amdgpu_waves_per_eu(2)))
+// offset known but the row stride; 0: any kernel.  DEALT: the grid of og_xcd, a
+// form of its own: the mapping's divisions at every workgroup's start cost the
+// other layers up to 2% (1x1 256 -> 512 at 28x28, batch 8, on a short base 494 ->
+// 485 us without them).
+template <int NCB, bool GARBLE, int K33, bool DEALT>
+__global__ void __launch_bounds__(kLinBlock) __attribute__((amdgpu_waves_per_eu(2, K33 > 0 ? 2 : 8)))
 k_linear_gemm(const LinPlan L, const uint8_t *__restrict__ planes, const uint8_t *__restrict__ prep,
               const int64_t *__restrict__ bias, const uint32_t *__restrict__ offsets, uint32_t *__restrict__ out) {
     extern __shared__ __align__(16) uint8_t lds[];
@@ -309,7 +314,7 @@ k_linear_gemm(const LinPlan L, const uint8_t *__restrict__ planes, const uint8_t
     // blockIdx.y: the words of the small moduli, with the most residues, are
     // dispatched first for every group) or every word of modulus blockIdx.y
     uint32_t pair = blockIdx.z, og = L.word_split ? blockIdx.y : blockIdx.z;
-    if (L.og_xcd) {
+    if constexpr (DEALT) {
         // workgroup 8 s + x runs on XCD x: its s-th (word, tile)
         const uint32_t x = blockIdx.x % kXcds, sl = blockIdx.x / kXcds;
         const uint32_t tiles = L.nimg * L.tile_rows * L.xtiles, t = sl / tiles;
@@ -905,23 +910,22 @@ int lin_allow_lds(const void *kernel, uint32_t bytes) {
                : REDASH_E_HIP;
 }
 
-template <int NCB, bool GARBLE, int K33>
+template <int NCB, bool GARBLE, int K33, bool DEALT = false>
 int launch_gemm(const LinPlan &L, const uint8_t *planes, const uint8_t *prep, const int64_t *bias,
                 const uint32_t *offsets, uint32_t *out, hipStream_t stream) {
-    int rc = lin_allow_lds(reinterpret_cast<const void *>(&k_linear_gemm<NCB, GARBLE, K33>), L.lds_bytes);
+    int rc = lin_allow_lds(reinterpret_cast<const void *>(&k_linear_gemm<NCB, GARBLE, K33, DEALT>), L.lds_bytes);
     if (rc) return rc;
     const uint64_t tiles = static_cast<uint64_t>(L.nimg) * L.tile_rows * L.xtiles;
     if (tiles >= (1ull << 31)) return REDASH_E_PARAM;
-    dim3 grid;
-    if (L.og_xcd) {
+    dim3 grid = L.word_split ? dim3(static_cast<uint32_t>(tiles), L.ogroups, L.npairs)
+                             : dim3(static_cast<uint32_t>(tiles), L.k, L.ogroups);
+    if constexpr (DEALT) {
         const uint64_t words = L.ogroups >= kXcds ? static_cast<uint64_t>(L.ogroups / kXcds) * L.npairs
                                                   : (L.npairs + kXcds / L.ogroups - 1) / (kXcds / L.ogroups);
         grid = dim3(static_cast<uint32_t>(kXcds * words * tiles));  // word_split: few
     }
-    hipLaunchKernelGGL((k_linear_gemm<NCB, GARBLE, K33>),
-                       L.og_xcd ? grid : L.word_split ? dim3(static_cast<uint32_t>(tiles), L.ogroups, L.npairs)
-                                    : dim3(static_cast<uint32_t>(tiles), L.k, L.ogroups),
-                       dim3(kLinBlock), L.lds_bytes, stream, L, planes, prep, bias, offsets, out);
+    hipLaunchKernelGGL((k_linear_gemm<NCB, GARBLE, K33, DEALT>), grid, dim3(kLinBlock), L.lds_bytes, stream, L, planes,
+                       prep, bias, offsets, out);
     return lin_launched();
 }
 
@@ -953,6 +957,8 @@ int launch_gemm_k(const LinPlan &L, const uint8_t *planes, const uint8_t *prep, 
         if (k33 && L.xstride == 80) return launch_gemm_w<NCB, GARBLE, 80>(L, planes, prep, bias, offsets, out, stream);
         return launch_gemm_w<NCB, GARBLE, 0>(L, planes, prep, bias, offsets, out, stream);
     }
+    if (L.og_xcd)  // flattened: 3x3, stride 1
+        return launch_gemm<NCB, GARBLE, 96, true>(L, planes, prep, bias, offsets, out, stream);
     if (L.kh == 3 && L.kw == 3 && L.ck == 64 && L.xstride == 96)
         return launch_gemm<NCB, GARBLE, 96>(L, planes, prep, bias, offsets, out, stream);
     if (L.kh == 3 && L.kw == 3 && L.ck == 64 && L.xstride == 80)
