@@ -962,24 +962,30 @@ __device__ __forceinline__ uint32_t mod64(int64_t x, uint32_t m) {
     return r;
 }
 
-// A workgroup takes 256 gadgets and one modulus (blockIdx.y): the modulus is
-// uniform, a small call still fills waves (65,536 gadgets over 10 primes: 49 us
-// with every modulus of a gadget on one lane), and a large one streams whole
-// kilobytes of each word.  P is a multiple of m_i: (x mod P) mod m_i = x mod m_i.
-template <int BLOCK>
+// A workgroup takes 256 gadgets and PER moduli (blockIdx.y the group of them):
+// the modulus is uniform, a small call still fills waves (65,536 gadgets over 10
+// primes: 40 us with every modulus of a gadget on one lane, 14.5 with one per
+// workgroup), and a large one streams whole kilobytes of each word.  P is a
+// multiple of m_i: (x mod P) mod m_i = x mod m_i.
+template <int BLOCK, uint32_t PER>
 __global__ void __launch_bounds__(BLOCK) k_encode(const Plan P, const int64_t *__restrict__ x,
                                                   const uint32_t *__restrict__ zero,
                                                   const uint32_t *__restrict__ offsets, uint32_t *__restrict__ lab) {
-    const uint32_t i = blockIdx.y;
     const uint64_t a = static_cast<uint64_t>(blockIdx.x) * BLOCK + threadIdx.x;
     if (a >= P.n) return;
     const uint64_t n = P.n;
-    const ModConst mc = P.mod[i];
-    const uint32_t v = mod64(x[a], mc.m);
-    const uint64_t base = static_cast<uint64_t>(mc.woff) * n + a;
-    for (uint32_t w = 0; w < mc.W; ++w)
-        lab[base + static_cast<uint64_t>(w) * n] =
-            label_axpy(zero[base + static_cast<uint64_t>(w) * n], offsets[mc.woff + w], v, w, mc);
+    const int64_t xa = x[a];
+#pragma unroll 1
+    for (uint32_t j = 0; j < PER; ++j) {
+        const uint32_t i = blockIdx.y * PER + j;
+        if (PER > 1 && i >= P.k) break;
+        const ModConst mc = P.mod[i];
+        const uint32_t v = mod64(xa, mc.m);
+        const uint64_t base = static_cast<uint64_t>(mc.woff) * n + a;
+        for (uint32_t w = 0; w < mc.W; ++w)
+            lab[base + static_cast<uint64_t>(w) * n] =
+                label_axpy(zero[base + static_cast<uint64_t>(w) * n], offsets[mc.woff + w], v, w, mc);
+    }
 }
 
 __global__ void k_zero_u64(uint64_t *p) { *p = 0; }
@@ -995,9 +1001,8 @@ static_assert(sizeof(Plan) + sizeof(CrtConst) + 6 * sizeof(void *) <= 4096, "dec
 // A workgroup takes 64 G gadgets with S waves per 64: wave (part, grp) checks
 // the labels over moduli part, part + S, ... of group grp and finds their
 // values; then the waves of part 0 sum the CRT terms of their gadgets (every
-// partial sum reduced below P < 2^63) and count the bad ones.  G = 1, S = k
-// for small calls (a wave per modulus), G = S = 4 for large ones, whose
-// workgroups then read whole kilobytes of each word.
+// partial sum reduced below P < 2^63) and count the bad ones.  G is at most 4
+// (the terms in LDS), G S at most 16.
 __global__ void __launch_bounds__(1024) k_decode(const Plan P, const CrtConst C, const uint32_t *__restrict__ Y,
                                                  const uint32_t *__restrict__ O, const uint32_t *__restrict__ offsets,
                                                  int64_t *__restrict__ y, unsigned long long *__restrict__ bad,
@@ -1387,8 +1392,19 @@ int redash_encode(const redash_params *p, const int64_t *d_x, const uint32_t *d_
     if (!d_offsets) return REDASH_E_NULL;
     if (P.n == 0) return REDASH_OK;
     if (!d_x || !d_in_zero || !d_in_labels) return REDASH_E_NULL;
-    hipLaunchKernelGGL(k_encode<256>, dim3(grid_for(P.n, 256), P.k), dim3(256), 0, stream, P, d_x, d_in_zero, d_offsets,
-                       d_in_labels);
+    // One modulus per workgroup while the call needs the workgroups; four, which
+    // read the values once for all of them, where their workgroups (two groups of
+    // moduli weigh as much as two moduli alone) pass 2^21 gadgets: 3,211,264
+    // gadgets: 12 primes 633 -> 592 us, 5 primes 303 -> 292, 4 moduli 202 -> 191;
+    // 800,000: 10 primes 142 -> 136; the other way at 1,100,000 with 3 and 4 moduli,
+    // 37.0 -> 40.2 and 63.5 -> 69.1, and at 400,000 with 12 primes, 74 -> 79.
+    const uint64_t groups = P.k == 2 ? 2 : (P.k + 3) / 4;
+    if (P.n * groups > (1u << 21))
+        hipLaunchKernelGGL((k_encode<256, 4>), dim3(grid_for(P.n, 256), (P.k + 3) / 4), dim3(256), 0, stream, P, d_x,
+                           d_in_zero, d_offsets, d_in_labels);
+    else
+        hipLaunchKernelGGL((k_encode<256, 1>), dim3(grid_for(P.n, 256), P.k), dim3(256), 0, stream, P, d_x, d_in_zero,
+                           d_offsets, d_in_labels);
     return launched();
 }
 
@@ -1477,8 +1493,23 @@ int redash_decode(const redash_params *p, const uint32_t *d_out_labels, const ui
         C.quot[i] = P.P / P.mod[i].m;
         C.inv[i] = inverse_mod(static_cast<uint32_t>(C.quot[i] % P.mod[i].m), P.mod[i].m);
     }
-    const bool wide = P.n > (1u << 18);
-    const uint32_t G = wide ? 4u : 1u, S = wide ? 4u : P.k;
+    // Waves per 64 gadgets (S) and groups of 64 per workgroup (G).  A small
+    // call takes a wave per modulus (12 primes, 65,536 gadgets: 69 us with every
+    // modulus on one lane, 22), with two groups where that makes workgroups of
+    // two waves (2 moduli, 262,144 gadgets: 21.6 us with one, 15.9).  A large one
+    // has waves enough: fewer of them per group leave fewer idle, those past the
+    // moduli or beside the one that sums.  From 4 moduli on S = 4 past 2^18 gadgets
+    // (12 moduli at 262,144: 77.4 -> 65.2 us) and 2 past 2^19 (400,000, S = 4 and 2:
+    // 4 moduli 36.6 and 37.7, 12 moduli 105.1 and 105.6; 3,211,264: 252 and 238, 756
+    // and 732, 6 moduli 475 and 405).  With 2 or 3 moduli S = 1 once it is the
+    // better (2 moduli, S = 2 and 1, at 200,704: 15.3 and 17.0, 400,000: 26.3 and
+    // 24.8, 3,211,264: 157 and 127; 3 moduli, S = 3 and 1, at 400,000: 25.4 and
+    // 29.3, 3,211,264: 173 and 165).
+    uint32_t G = P.k == 2 ? 2u : 1u, S = P.k;
+    if (P.n > (1u << (P.k == 3 ? 19 : 18))) {
+        S = P.k <= 3 ? 1u : P.n > (1u << 19) ? 2u : 4u;
+        G = S == 2 ? 2u : 4u;
+    }
     hipLaunchKernelGGL(k_decode, dim3(grid_for(P.n, static_cast<int>(64 * G))), dim3(64 * G * S), 0, stream, P, C,
                        d_out_labels, d_out_zero, d_offsets, d_y, bad, G, S);
     return launched();

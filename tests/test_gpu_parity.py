@@ -629,6 +629,49 @@ def test_encode_reduces_any_value_and_decode_counts_each_bad_gadget(moduli, S):
     assert [int(y[a]) for a in good] == [want[a] for a in good]
 
 
+# Encode takes one modulus per workgroup up to 2^20 gadgets (2^21 with 3 or 4
+# moduli, less with more than 8) and four above; decode gives 64 gadgets as many
+# waves as there are moduli up to 2^18 gadgets (2^19 with 3 moduli; two groups
+# of 64 per workgroup with 2), then four, and two above 2^19 (one with up to 3
+# moduli), two or four groups per workgroup.
+DECODE_SIZES = [(1 << 17) + 65, 1 << 18, (1 << 18) + 1, (1 << 18) + 64 * 3 + 17, 1 << 19, (1 << 19) + 64 * 2 + 1,
+                (1 << 20), (1 << 20) + 64 + 3, (1 << 21) + 5]
+
+
+@pytest.mark.parametrize("n", DECODE_SIZES)
+@pytest.mark.parametrize("moduli,S", [((2, 3), (1,)), ((32, 97, 107), (0,)), ((3, 4, 5, 7, 11, 13), (1,))])
+def test_decode_launch_shapes_count_each_bad_gadget(moduli, S, n):
+    """Corrupted labels in every 64-gadget group of a workgroup, in the first
+    and the last modulus, in the last (partial) group; the last word of several
+    moduli of one gadget, which counts once."""
+    P = rns.cardinality(moduli)
+    bp = B.make_params(moduli, S, n, 78)
+    x = np.random.default_rng(n).integers(-(P // 2), P - P // 2, size=n, dtype=np.int64)
+    buf = B.Buffers(bp)
+    B.redash_garble_scale(bp, buf.offsets, buf.in_zero, buf.out_zero, buf.tables, buf.work)
+    B.redash_encode(bp, torch.from_numpy(x).cuda(), buf.in_zero, buf.offsets, buf.in_labels)
+    torch.cuda.synchronize()
+    op = O.make_params(list(moduli), list(S), n, 78)
+    assert np.array_equal(H.to_u32(buf.in_labels), O.encode(op, x, H.to_u32(buf.in_zero), H.to_u32(buf.offsets)))
+    lay, _ = H.label_layout(moduli)
+    lab = buf.in_labels.clone()
+    bad = {}
+    for group in (0, 1, 2, 3, 5, 1002, (n - 1) // 64):
+        for i, lane in ((0, 0), (len(moduli) - 1, 31), (len(moduli) // 2, 63)):
+            bad[min(64 * group + lane, n - 1)] = (i,)
+    bad[64 * 4 + 9] = tuple(range(len(moduli)))
+    for a, where in bad.items():
+        for i in where:
+            woff, W = lay[i]
+            lab[(woff + W - 1) * n + a] ^= 1
+    B.redash_decode(bp, lab, buf.in_zero, buf.offsets, buf.y, buf.bad)
+    torch.cuda.synchronize()
+    assert int(buf.bad.item()) == len(bad)
+    good = np.ones(n, bool)
+    good[list(bad)] = False
+    assert np.array_equal(buf.y.cpu().numpy()[:n][good], x[good])
+
+
 # The smallest calls: up to 20 gadgets per CU share a workgroup (a lane per gate
 # and gadget hashes, a lane per gadget and word updates; above 10 gadgets the
 # words of a gate take two waves).  (name, base, scaling, gadgets per CU, extra)
