@@ -1249,12 +1249,16 @@ uint32_t split_for(uint64_t count, uint64_t cus) {
 // after them instead of running as a last round with few waves per SIMD, whose
 // gadgets would take the latency of their gate chain (12 primes: 3,211,264
 // gadgets, 65,536 over six rounds, 7.35 -> 7.00 ms; 622,592 1.57 -> 1.46; a
-// rest of 175,712 costs the same either way).  A chain of few gates is short
-// enough as it is (5 gates, 65,536 over: 0.558 ms against 0.570).  A larger
-// rest over one round makes two even rounds of smaller workgroups: a CU whose
-// two workgroups end together would otherwise take two full ones of the rest
-// and another CU none (802,816 gadgets 2.12 -> 1.90 ms; no gain from three
-// rounds on).
+// rest of 175,712 costs the same either way).  Over rests of 8,192 to 98,304 after
+// 1, 2, 3 and 6 rounds the split takes 0.88 to 1.02 of the time of k_eval for the
+// rest with 14, 20, 27, 35, 54 and 77 gates (no base has 11 to 13), 0.91 to 1.07
+// with 9 and 10 and 0.97 to 1.06 with 5, whose chains are short enough as they
+// are: there only a rest of up to 32,768 goes to it.  A larger rest over one
+// round makes two even rounds of smaller workgroups: a CU whose two workgroups
+// end together would otherwise take two full ones of the rest and another CU
+// none (802,816 gadgets 2.12 -> 1.90 ms).  Three even rounds take 0.94 to 1.07 of
+// the time, as the rest falls (131,072 over two: 0.96, 200,000: 1.05, 300,000:
+// 0.97), four or seven 1.00 to 1.08.
 int launch_eval(const Plan &P, uint32_t lds, const uint32_t *in, const uint32_t *tab, uint32_t *out, uint32_t *work,
                 hipStream_t stream) {
     DeviceInfo d;
@@ -1286,7 +1290,7 @@ int launch_eval(const Plan &P, uint32_t lds, const uint32_t *in, const uint32_t 
     const uint64_t round = 2 * ncu * kLaneBlock;  // gadgets of one round, one per lane
     uint64_t bulk = P.n;
     const uint64_t rest = P.n % round;
-    if (P.n > round && rest > 0 && rest <= (P.G >= 16 ? 2 * ncu * split_most(4) : 2 * ncu * 64)) bulk = P.n - rest;
+    if (P.n > round && rest > 0 && rest <= (P.G >= 14 ? 2 * ncu * split_most(4) : 2 * ncu * 64)) bulk = P.n - rest;
     if ((rc = allow_lds(reinterpret_cast<const void *>(&k_eval<kLaneBlock>), lds))) return rc;
     int block = 0;
     if ((rc = block_for(bulk > round && bulk < 2 * round ? (bulk + 1) / 2 : bulk, kLaneBlock, &block))) return rc;

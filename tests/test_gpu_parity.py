@@ -453,28 +453,25 @@ def test_full_size_batched():
     _check_full(WL.BATCHED, 4096, 4096, 8192, 32)
 
 
-# The evaluator's launch thresholds on this GPU.  Calls of up to one round of
-# two workgroups per CU with 64, 192 or 384 gadgets per workgroup give each
+# The split evaluator's launch thresholds on this GPU.  Calls of up to one round
+# of two workgroups per CU with 64, 192 or 384 gadgets per workgroup give each
 # group of 64 gadgets 12, 4 or 2 waves; a call above one full round of the 4-
 # or 2-wave split by at most 64 gadgets per CU runs that round on the split and
 # the rest on 12 waves per 64 gadgets in the same launch; larger calls take
-# one gadget per lane on whole rounds of 768-gadget workgroups, and a rest that
-# the 12-wave split holds in one round (64 gadgets per workgroup) goes to it,
-# starting at the first gadget after the rounds.  Each threshold and one gadget
-# past it.  (name, whole rounds, gadgets per workgroup of the two per CU,
-# gadgets per CU, extra): n = 2 cus (768 rounds + per) + cus per_cu + extra.
-LAUNCH_EDGES = [("split12-last", 0, 64, 0, 0), ("split4-first", 0, 64, 0, 1), ("split4-last", 0, 192, 0, 0),
-                ("split4-round-rest-first", 0, 192, 0, 1), ("split4-round-rest-last", 0, 192, 64, 0),
-                ("split2-first", 0, 192, 64, 1), ("split2-last", 0, 384, 0, 0),
-                ("split2-round-rest-first", 0, 384, 0, 1), ("split2-round-rest-last", 0, 384, 64, 0),
-                ("one-per-lane-first", 0, 384, 64, 1), ("round-rest-one", 1, 0, 0, 1),
-                ("round-rest-split12-last", 1, 64, 0, 0), ("round-rest-past-split12", 1, 64, 0, 1)]
+# one gadget per lane (LANE_EDGES).  Each threshold and one gadget past it.
+# (name, gadgets per workgroup of the two per CU, gadgets per CU, extra): n = 2
+# cus per + cus per_cu + extra.
+LAUNCH_EDGES = [("split12-last", 64, 0, 0), ("split4-first", 64, 0, 1), ("split4-last", 192, 0, 0),
+                ("split4-round-rest-first", 192, 0, 1), ("split4-round-rest-last", 192, 64, 0),
+                ("split2-first", 192, 64, 1), ("split2-last", 384, 0, 0),
+                ("split2-round-rest-first", 384, 0, 1), ("split2-round-rest-last", 384, 64, 0),
+                ("one-per-lane-first", 384, 64, 1)]
 
 
-@pytest.mark.parametrize("rounds,per,per_cu,extra", [e[1:] for e in LAUNCH_EDGES], ids=[e[0] for e in LAUNCH_EDGES])
-def test_evaluator_launch_thresholds(rounds, per, per_cu, extra):
+@pytest.mark.parametrize("per,per_cu,extra", [e[1:] for e in LAUNCH_EDGES], ids=[e[0] for e in LAUNCH_EDGES])
+def test_evaluator_launch_thresholds(per, per_cu, extra):
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    n = 2 * cus * (768 * rounds + per) + cus * per_cu + extra
+    n = 2 * cus * per + cus * per_cu + extra
     P = rns.cardinality(WL.PRIMES_12)
     w = WL.Workload(f"edge-{n}", tuple(WL.PRIMES_12), (11,), n, 60 + per + per_cu + extra, "uniform", -(P // 2),
                     P - P // 2)
@@ -566,16 +563,19 @@ def test_one_gadget_per_lane_on_varied_bases(name, moduli, S):
 
 # One gadget per lane: rounds of two 1,024-gadget workgroups per CU.  A rest of
 # up to 192 gadgets per workgroup of a round goes to the 12- and 4-wave splits
-# (64 on chains of fewer than 16 gates), a larger one over a single round
+# (64 on chains of fewer than 14 gates), a larger one over a single round
 # makes two even rounds.  (name, base, scaling, gadgets per workgroup of the
 # two per CU, extra)
 LANE_EDGES = [("round-last", tuple(WL.PRIMES_12), (11,), 1024, 0),
+              ("rest-one", tuple(WL.PRIMES_12), (11,), 1024, 1),
+              ("rest-split12-last", tuple(WL.PRIMES_12), (11,), 1024 + 64, 0),
               ("rest-split4-first", tuple(WL.PRIMES_12), (11,), 1024 + 64, 1),
               ("rest-split4-last", tuple(WL.PRIMES_12), (10, 11), 1024 + 192, 0),
               ("even-halves-first", tuple(WL.PRIMES_12), (11,), 1024 + 192, 1),
               ("even-halves-ragged", tuple(WL.PRIMES_12[:8]), (2,), 2047, 63),
               ("two-rounds-rest", (3, 5, 7, 8, 11, 13, 17, 19), (3,), 2048 + 100, 7),
-              ("few-gates-rest", (32, 97, 107), (0,), 1024 + 64, 1)]
+              ("few-gates-rest", (32, 97, 107), (0,), 1024 + 64, 1),
+              ("14-gates-rest-split4-first", (2, 3, 5, 7, 11), (4,), 1024 + 64, 1)]
 
 
 @pytest.mark.parametrize("name,moduli,S,per,extra", LANE_EDGES, ids=[e[0] for e in LANE_EDGES])
@@ -762,7 +762,7 @@ def test_one_gadget_per_lane_on_random_bases(name, moduli, S):
 # split, a full 4-wave round and its rest, the 2-wave split, a full 2-wave
 # round and its rest, and whole one-gadget-per-lane rounds with a rest.
 REGIME_SIZES = [("split12", 0, 60, 7), ("split4", 0, 250, 11), ("split4-round-rest", 2 * 192, 40, 3),
-                ("split2", 0, 600, 13), ("split2-round-rest", 2 * 384, 20, 5), ("lane-rounds-rest", 2 * 768, 100, 9)]
+                ("split2", 0, 600, 13), ("split2-round-rest", 2 * 384, 20, 5), ("lane-rounds-rest", 2 * 1024, 100, 9)]
 REGIME_BASES = [b for b in _random_bases(60, 3131) if len(b[1]) <= 6][: len(REGIME_SIZES)]
 
 
