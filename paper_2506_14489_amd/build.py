@@ -29,7 +29,6 @@ FLAGS = [
     # no packed-FP32 instructions anywhere in the device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall",
-    "-Wno-unused-function",
 ]
 
 

@@ -350,13 +350,6 @@ __device__ __forceinline__ uint32_t word_axpy(uint32_t y, uint32_t x, uint32_t c
     return out;
 }
 
-// y - x, residue by residue (m > 2).
-__device__ __forceinline__ uint32_t word_sub(uint32_t y, uint32_t x, uint32_t nres, const ModConst &mc) {
-    uint32_t out = 0;
-    for (uint32_t j = 0; j < nres; ++j) out |= sub_mod(field(y, j, mc), field(x, j, mc), mc.m) << (mc.b * j);
-    return out;
-}
-
 // c (y - x), residue by residue (m > 2).
 __device__ __forceinline__ uint32_t word_scaled_sub(uint32_t y, uint32_t x, uint32_t c, uint32_t nres,
                                                     const ModConst &mc) {
@@ -371,10 +364,6 @@ __device__ __forceinline__ uint32_t word_scaled_sub(uint32_t y, uint32_t x, uint
 __device__ __forceinline__ uint32_t label_axpy(uint32_t y, uint32_t x, uint32_t c, uint32_t w, const ModConst &mc) {
     if (mc.m == 2) return (c & 1u) ? (y ^ x) : y;
     return word_axpy(y, x, c, residues_in_word(w, mc), mc);
-}
-__device__ __forceinline__ uint32_t label_sub(uint32_t y, uint32_t x, uint32_t w, const ModConst &mc) {
-    if (mc.m == 2) return y ^ x;
-    return word_sub(y, x, residues_in_word(w, mc), mc);
 }
 __device__ __forceinline__ uint32_t label_scaled_sub(uint32_t y, uint32_t x, uint32_t c, uint32_t w,
                                                      const ModConst &mc) {
@@ -421,12 +410,6 @@ __device__ __forceinline__ uint32_t digits_word(uint32_t (&V)[8], uint32_t w, co
         D = q;
     }
     return out | D;  // the most significant digit is residue 0 of the word
-}
-
-// floor(x / d) for a 32-bit x with constants from division_constants().
-__device__ __forceinline__ uint32_t div_const(uint32_t x, uint32_t M, uint32_t s, uint32_t fix) {
-    const uint32_t t = __umulhi(x, M);
-    return fix ? (t + ((x - t) >> 1)) >> s : t >> s;
 }
 
 // Evaluator fast path for one packed word over Z_m (m > 2, mc.fast set), any
@@ -720,10 +703,10 @@ __device__ __forceinline__ void hash_fraction(const uint32_t *T, uint32_t x0, ui
     V[7] = h3;
 }
 
-// The two-block hashes of NG gates, the AES blocks of all of them round by
-// round.  x: the folded input label that the gates share, gate j under tweak
-// tweak() + j (called before and after the rounds); V[j] receives the 256-bit fraction: limbs 0-3 are the output words
-// of block 0, 4-7 of block 1.
+// The two-block hash of a gate, the two AES blocks round by round.  x: the
+// folded input label; tweak() is called before and after the rounds; V receives
+// the 256-bit fraction: limbs 0-3 are the output words of block 0, 4-7 of block
+// 1.
 //
 // The two blocks of a hash differ in bit 0 of word 0 alone (4 tau and 4 tau +
 // 1), so they share 15 of the 16 lookups of round 1 and 12 of round 2.  Pads
@@ -731,86 +714,77 @@ __device__ __forceinline__ void hash_fraction(const uint32_t *T, uint32_t x0, ui
 // through a carry (see pad_words_top), and without `all` they are not
 // computed (3 of block 0's 4 last-round columns).  Per hash 281 lookups
 // instead of 320.
-template <int NG, typename Key, typename Tweak>
-__device__ __forceinline__ void hash_pairs(const PermTE02 &T, const Key &K, const uint32_t (&x)[4], Tweak &&tweak,
-                                           uint32_t gid, bool all, uint32_t (&V)[NG][8]) {
-    uint32_t s[2 * NG][4];
+template <typename Key, typename Tweak>
+__device__ __forceinline__ void hash_pair(const PermTE02 &T, const Key &K, const uint32_t (&x)[4], Tweak &&tweak,
+                                          uint32_t gid, bool all, uint32_t (&V)[8]) {
+    uint32_t s[2][4];
     const uint64_t tau = tweak();
     __builtin_amdgcn_s_setprio(1);  // as in aes128_encrypt_n
-#pragma unroll
-    for (int j = 0; j < NG; ++j) {
-        const uint64_t tw = (tau + static_cast<uint64_t>(j)) * 4u;
+    {
+        const uint64_t tw = tau * 4u;
         const uint32_t w[4] = {xor3(x[2], static_cast<uint32_t>(tw), K(0)),
                                xor3(x[3], static_cast<uint32_t>(tw >> 32), K(1)), xor3(x[2], x[0], K(2)),
                                xor3(x[3], x[1], K(3) ^ gid)};
         uint32_t c[4];
         const uint32_t c01 = T.first_round_pair(w, K, c);
         __builtin_amdgcn_sched_barrier(0);
-        T.second_round_pair(c, c01, K, s[2 * j], s[2 * j + 1]);
+        T.second_round_pair(c, c01, K, s[0], s[1]);
         __builtin_amdgcn_sched_barrier(0);
     }
     // Rounds 3..9 stay a loop (the instruction cache then holds the gate loop),
     // three rounds a pass: a block's new state needs four registers of its own
     // while the old one is read, and after three rounds of two blocks over
     // three register sets every state is back where it began, without copies.
-    auto round_to = [&](const uint32_t(&in)[2 * NG][4], uint32_t(&o)[2 * NG][4], int r) {
+    auto round = [&](int r) {
 #pragma unroll
-        for (int b = 0; b < 2 * NG; ++b) {
-            const uint32_t s0 = in[b][0], s1 = in[b][1], s2 = in[b][2], s3 = in[b][3];
-            o[b][0] = T.column(s0, s1, s2, s3, K, 4 * r);
-            o[b][1] = T.column(s1, s2, s3, s0, K, 4 * r + 1);
-            o[b][2] = T.column(s2, s3, s0, s1, K, 4 * r + 2);
-            o[b][3] = T.column(s3, s0, s1, s2, K, 4 * r + 3);
-        }
-    };
-    auto last_round = [&](const uint32_t(&in)[2 * NG][4]) {
-#pragma unroll
-        for (int j = 0; j < NG; ++j) {
-            const uint32_t a0 = in[2 * j][0], a1 = in[2 * j][1], a2 = in[2 * j][2], a3 = in[2 * j][3];
-            V[j][3] = T.last_column(a3, a0, a1, a2, K, 43);
-            V[j][0] = V[j][1] = V[j][2] = 0;
-            if (all) {
-                V[j][0] = T.last_column(a0, a1, a2, a3, K, 40);
-                V[j][1] = T.last_column(a1, a2, a3, a0, K, 41);
-                V[j][2] = T.last_column(a2, a3, a0, a1, K, 42);
-            }
-            const uint32_t b0 = in[2 * j + 1][0], b1 = in[2 * j + 1][1], b2 = in[2 * j + 1][2], b3 = in[2 * j + 1][3];
-            V[j][4] = T.last_column(b0, b1, b2, b3, K, 40);
-            V[j][5] = T.last_column(b1, b2, b3, b0, K, 41);
-            V[j][6] = T.last_column(b2, b3, b0, b1, K, 42);
-            V[j][7] = T.last_column(b3, b0, b1, b2, K, 43);
+        for (int b = 0; b < 2; ++b) {
+            const uint32_t s0 = s[b][0], s1 = s[b][1], s2 = s[b][2], s3 = s[b][3];
+            s[b][0] = T.column(s0, s1, s2, s3, K, 4 * r);
+            s[b][1] = T.column(s1, s2, s3, s0, K, 4 * r + 1);
+            s[b][2] = T.column(s2, s3, s0, s1, K, 4 * r + 2);
+            s[b][3] = T.column(s3, s0, s1, s2, K, 4 * r + 3);
         }
     };
 #pragma unroll 1
     for (int r = 3; r < 9; r += 3) {
-        round_to(s, s, r);
-        round_to(s, s, r + 1);
-        round_to(s, s, r + 2);
+        round(r);
+        round(r + 1);
+        round(r + 2);
     }
-    round_to(s, s, 9);
-    last_round(s);
+    round(9);
+    {
+        const uint32_t a0 = s[0][0], a1 = s[0][1], a2 = s[0][2], a3 = s[0][3];
+        V[3] = T.last_column(a3, a0, a1, a2, K, 43);
+        V[0] = V[1] = V[2] = 0;
+        if (all) {
+            V[0] = T.last_column(a0, a1, a2, a3, K, 40);
+            V[1] = T.last_column(a1, a2, a3, a0, K, 41);
+            V[2] = T.last_column(a2, a3, a0, a1, K, 42);
+        }
+        const uint32_t b0 = s[1][0], b1 = s[1][1], b2 = s[1][2], b3 = s[1][3];
+        V[4] = T.last_column(b0, b1, b2, b3, K, 40);
+        V[5] = T.last_column(b1, b2, b3, b0, K, 41);
+        V[6] = T.last_column(b2, b3, b0, b1, K, 42);
+        V[7] = T.last_column(b3, b0, b1, b2, K, 43);
+    }
     __builtin_amdgcn_s_setprio(0);
     // Matyas-Meyer-Oseas feed-forward of the block input u ^ T.  The inputs
     // are formed again from x and tau rather than kept through the rounds
     // (opaque keeps the compiler from reusing the earlier values).
     const uint32_t y0 = opaque(x[0]), y1 = opaque(x[1]), y2 = opaque(x[2]), y3 = opaque(x[3]);
-    const uint64_t tau2 = tweak();
-#pragma unroll
-    for (int j = 0; j < NG; ++j) {
-        const uint64_t tw = (tau2 + static_cast<uint64_t>(j)) * 4u;
-        const uint32_t lo = y2 ^ static_cast<uint32_t>(tw), hi = y3 ^ static_cast<uint32_t>(tw >> 32);
-        const uint32_t u2 = y2 ^ y0, u3 = xor3(y3, y1, gid);
-        V[j][3] ^= u3;
-        if (all) {
-            V[j][0] ^= lo;
-            V[j][1] ^= hi;
-            V[j][2] ^= u2;
-        }
-        V[j][4] ^= lo ^ 1u;
-        V[j][5] ^= hi;
-        V[j][6] ^= u2;
-        V[j][7] ^= u3;
+    const uint64_t tw = tweak() * 4u;
+    const uint32_t lo = y2 ^ static_cast<uint32_t>(tw), hi = y3 ^ static_cast<uint32_t>(tw >> 32);
+    const uint32_t u2 = y2 ^ y0, u3 = xor3(y3, y1, gid);
+    V[3] ^= u3;
+    if (all) {
+        V[0] ^= lo;
+        V[1] ^= hi;
+        V[2] ^= u2;
     }
+    V[4] ^= lo ^ 1u;
+    V[5] ^= hi;
+    V[6] ^= u2;
+    V[7] ^= u3;
 }
 
 // Limbs 0-2 of the fraction: the rest of block 0's output (the rare case).

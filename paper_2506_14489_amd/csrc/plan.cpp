@@ -158,7 +158,6 @@ void fill_mod_const(uint32_t m, ModConst *mc) {
         mc->sw_ones |= 1u << (mc->b * f);
         mc->sw_k |= ((1u << mc->b) - m) << (mc->b * f);
     }
-    mc->two_m = 2 * m;
     if (full_word) return;  // no fast constants: the packed-add fields above are all it uses
     mc->red_M = static_cast<uint32_t>(((1ull << 32) + m - 1) / m);
     // x m < 2^32 for x < 3 m^2 (every m <= 255); five or six words (every m

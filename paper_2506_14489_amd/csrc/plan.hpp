@@ -51,7 +51,6 @@ struct ModConst {
     //    _f: full words, _l: the last word.  (Separate fields, not arrays:
     //    a selected array element would be indexed at run time.)
     uint32_t fast;
-    uint32_t two_m;  // 2m
     uint32_t red_M, sd_M, sd_s;
     uint32_t nlo_f, pw_lo_f, lo_M_f, lo_s_f;
     uint32_t nlo_l, pw_lo_l, lo_M_l, lo_s_l;

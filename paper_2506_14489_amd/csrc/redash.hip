@@ -410,7 +410,7 @@ k_eval(const EvalPlan P, const uint32_t *__restrict__ in, const uint32_t *__rest
 #pragma unroll 1
             for (uint32_t j = 0; j < ng; ++j) {
                 uint32_t e = P.egate[g + j];
-                uint32_t row[kMaxW], V[1][8], D[kMaxW];
+                uint32_t row[kMaxW], V[8], D[kMaxW];
                 static_for<kMaxW>([&](auto w) { row[w] = 0; });
                 {
                     const uint32_t W = P.mod[eg_dst(e)].W;
@@ -419,16 +419,16 @@ k_eval(const EvalPlan P, const uint32_t *__restrict__ in, const uint32_t *__rest
                         const uint64_t at = static_cast<uint64_t>(eg_toff(e)) * P.n - W;
                         load_row(row, tab + mad64(opaque(colour), W, mad64(opaque(LB.aoff) >> 2, (q - 1) * W, at)), W);
                     }
-                    hash_pairs<1>(TT, LdsKey{K}, x, [&] { return gate_tweak(P, opaque_here(LB.aoff) >> 2, g + j); }, P.gid,
+                    hash_pair(TT, LdsKey{K}, x, [&] { return gate_tweak(P, opaque_here(LB.aoff) >> 2, g + j); }, P.gid,
                                   P.mod[eg_dst(e)].pad_amb == 0, V);
                 }
                 // (the modulus's constants are loaded here, not held in scalar
                 // registers through the hash)
                 asm volatile("" : "+s"(e));
                 const ModConst mm = P.mod[eg_dst(e)];
-                gate_pad<true>(TT, K, P.gid, mm, V[0], D, digit,
+                gate_pad<true>(TT, K, P.gid, mm, V, D, digit,
                                [&] { return gate_tweak(P, opaque(LB.aoff) >> 2, g + j); });
-                reg_update<true>(g + j, e, mm, V[0], D, row, T[0]);
+                reg_update<true>(g + j, e, mm, V, D, row, T[0]);
                 if (two) swap_slots(T);
             }
             if (alone1) swap_slots(T);
@@ -520,13 +520,13 @@ k_eval_split(const SplitPlan P, const uint32_t *__restrict__ in, const uint32_t 
                 load_row(row, tab + static_cast<uint64_t>(P.goff[g + i]) * P.n + (a * (q - 1) + (colour - 1)) * Wd, Wd);
             uint32_t T[kMaxW];
             load_label(T, LB, gate_tsrc(d), mm, gate_tsrc(d) != kLocZero);
-            uint32_t Vn[1][8], D[kMaxW];
-            hash_pairs<1>(TT, LdsKey{K}, x, [&] { return opaque64(tau0 + g + i); }, P.gid, mm.pad_amb == 0, Vn);
-            gate_pad<false>(TT, K, P.gid, mm, Vn[0], D,
+            uint32_t V[8], D[kMaxW];
+            hash_pair(TT, LdsKey{K}, x, [&] { return opaque64(tau0 + g + i); }, P.gid, mm.pad_amb == 0, V);
+            gate_pad<false>(TT, K, P.gid, mm, V, D,
                             [&](uint32_t(&f)[4]) { static_for<4>([&](auto l) { f[l] = x[l]; }); },
                             [&] { return tau0 + g + i; });
             const uint32_t e = gate_dst(d) | (gate_kind(d) << 4) | (gate_tab(d) << 5) | (gate_coeff(d) << 6);
-            reg_update<false>(g + i, e, mm, Vn[0], D, row, T);
+            reg_update<false>(g + i, e, mm, V, D, row, T);
             store_label(T, LB, gate_tdst(d), mm);
         }
         __syncthreads();
@@ -662,10 +662,10 @@ k_eval_small(const SplitPlan P, const uint32_t *__restrict__ in, const uint32_t 
         // Hashes: job i c + gl is gate g + i of gadget gl.
         if (wave * 64 < r * c) {
             const uint32_t job = tid < r * c ? tid : r * c - 1, i = job / c, gl = job % c;
-            uint32_t x[4], V[1][8];
+            uint32_t x[4], V[8];
             digit(gl, x);
-            hash_pairs<1>(TT, LdsKey{K}, x, [&] { return opaque64((P.a0 + a0 + gl) * P.G + g + i); }, P.gid, all, V);
-            if (tid < r * c) static_for<8>([&](auto l) { Vb[l * (r * c) + job] = V[0][l]; });
+            hash_pair(TT, LdsKey{K}, x, [&] { return opaque64((P.a0 + a0 + gl) * P.G + g + i); }, P.gid, all, V);
+            if (tid < r * c) static_for<8>([&](auto l) { Vb[l * (r * c) + job] = V[l]; });
         }
         __syncthreads();
         // Updates.
@@ -914,14 +914,14 @@ k_garble(const Plan P, const SeedKey key, const uint32_t *__restrict__ offsets, 
                 });
             }
             // the packed pad of the label A under the gate's tweak
-            uint32_t x[4], V[1][8], D[kMaxW];
+            uint32_t x[4], V[8], D[kMaxW];
             fold_label(A, P.mod[gate_src(dc)], x);
             auto tweak = [&] { return opaque64(tau0 + g); };
-            hash_pairs<1>(TT, HK, x, tweak, P.gid, P.mod[gate_dst(dc)].pad_amb == 0, V);
+            hash_pair(TT, HK, x, tweak, P.gid, P.mod[gate_dst(dc)].pad_amb == 0, V);
             asm volatile("" : "+s"(dc));
             const ModConst mm = P.mod[gate_dst(dc)];
             gate_pad<true>(
-                TT, K, P.gid, mm, V[0], D, [&](uint32_t(&f)[4]) { fold_label(A, P.mod[gate_src(dc)], f); }, tweak);
+                TT, K, P.gid, mm, V, D, [&](uint32_t(&f)[4]) { fold_label(A, P.mod[gate_src(dc)], f); }, tweak);
             pack_pad(D, mm);
             if (c != 0) {
                 // colours 1..q-1: the row B_c - H(A_{v_c})
@@ -1144,14 +1144,10 @@ int cached_plan(const redash_params *p, const Plan **out) {
     return REDASH_OK;
 }
 
-// The evaluator schedule of P (the cached plan's, kept with it).
-const EvalPlan &eval_plan(const Plan &P) {
+// The evaluator schedule and the runs of the cached plan, which every entry
+// point launches from (cached_plan), kept with it.
+const EvalPlan &eval_plan() {
     PlanCache &c = t_plan;
-    if (&P != &c.P) {  // not reached: every entry point takes its plan from the cache
-        static thread_local EvalPlan E;
-        build_eval_plan(P, &E);
-        return E;
-    }
     if (!c.has_eval) {
         build_eval_plan(c.P, &c.E);
         c.has_eval = true;
@@ -1159,14 +1155,8 @@ const EvalPlan &eval_plan(const Plan &P) {
     return c.E;
 }
 
-// The runs of P, likewise.
-const SplitPlan &split_plan(const Plan &P) {
+const SplitPlan &split_plan() {
     PlanCache &c = t_plan;
-    if (&P != &c.P) {  // not reached, as above
-        static thread_local SplitPlan S;
-        build_split_plan(P, &S);
-        return S;
-    }
     if (!c.has_split) {
         build_split_plan(c.P, &c.S);
         c.has_split = true;
@@ -1284,7 +1274,7 @@ int launch_eval(const Plan &P, uint32_t lds, const uint32_t *in, const uint32_t 
         if (bytes <= static_cast<uint32_t>(d.max_lds)) {
             if ((rc = allow_lds(reinterpret_cast<const void *>(&k_eval_small<kEvalBlock>), bytes))) return rc;
             hipLaunchKernelGGL(k_eval_small<kEvalBlock>, dim3(grid_for(P.n, static_cast<int>(per))), dim3(kEvalBlock),
-                               bytes, stream, split_plan(P), in, tab, out, SmallLaunch{per});
+                               bytes, stream, split_plan(), in, tab, out, SmallLaunch{per});
             return launched();
         }
     }
@@ -1294,12 +1284,12 @@ int launch_eval(const Plan &P, uint32_t lds, const uint32_t *in, const uint32_t 
         if (P.n > full && P.n - full <= ncu * 64) {
             const uint32_t nb0 = static_cast<uint32_t>(2 * ncu);
             const unsigned grid = nb0 + grid_for(P.n - full, 64);
-            return launch_split_kernel(split_plan(P), lds, in, tab, out, work, SplitLaunch{0, nb0, split, 12}, grid, kEvalBlock,
+            return launch_split_kernel(split_plan(), lds, in, tab, out, work, SplitLaunch{0, nb0, split, 12}, grid, kEvalBlock,
                                        stream);
         }
     }
     if (const uint32_t split = split_for(P.n, ncu))
-        return launch_split(split, split_plan(P), lds, in, tab, out, work, 0, P.n, stream);
+        return launch_split(split, split_plan(), lds, in, tab, out, work, 0, P.n, stream);
     const uint64_t round = 2 * ncu * kLaneBlock;  // gadgets of one round, one per lane
     uint64_t bulk = P.n;
     const uint64_t rest = P.n % round;
@@ -1307,12 +1297,12 @@ int launch_eval(const Plan &P, uint32_t lds, const uint32_t *in, const uint32_t 
     if ((rc = allow_lds(reinterpret_cast<const void *>(&k_eval<kLaneBlock>), lds))) return rc;
     int block = 0;
     if ((rc = block_for(bulk > round && bulk < 2 * round ? (bulk + 1) / 2 : bulk, kLaneBlock, &block))) return rc;
-    const EvalPlan &E = eval_plan(P);
+    const EvalPlan &E = eval_plan();
     hipLaunchKernelGGL(k_eval<kLaneBlock>, dim3(grid_for(bulk, block)), dim3(block), lds, stream, E, in, tab, out,
                        work);
     if ((rc = launched())) return rc;
     if (bulk == P.n) return REDASH_OK;
-    return launch_split(split_for(P.n - bulk, ncu), split_plan(P), lds, in, tab, out, work, bulk, P.n - bulk, stream);
+    return launch_split(split_for(P.n - bulk, ncu), split_plan(), lds, in, tab, out, work, bulk, P.n - bulk, stream);
 }
 
 

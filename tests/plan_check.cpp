@@ -197,7 +197,6 @@ static void check_modulus(uint32_t m) {
     check_pad(mc);
     // one reduction per residue: floor(x/m) = umulhi(x, ceil(2^32/m)) for x < 3 m^2
     for (uint32_t x = 0; x < 3 * m * m; ++x) CHECK(umulhi(x, mc.red_M) == x / m, "m=%u red x=%u", m, x);
-    CHECK(mc.two_m == 2 * m, "m=%u two_m", m);
     // the digit split of a word D < m^nres at m^nlo, for full and last words
     uint64_t part = 1;
     for (int k = 0; k < 2; ++k) {
