@@ -25,8 +25,11 @@ if ROOT not in sys.path:
 
 METRIC = "garbled scaling gadgets evaluated/sec (1 GPU) + % HBM roofline"
 HBM_PEAK_GBS = 8000.0
-# int32 vector ALU: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (one lane-op per lane per clock)
-ALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
+# int32 vector ALU: 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz.  A wave64 and, or, xor,
+# add or three-input logic operation takes a SIMD 2.1-2.5 cycles (measured), so
+# 32 lanes; multiplies, byte permutes, left shifts and bit-field operations take
+# twice as long, so this roof is out of reach for code that needs those
+ALU_PEAK_TOPS = 256 * 4 * 32 * 2.4e9 / 1e12
 # LDS: 128 bytes per clock per CU (32 banks x 4 bytes)
 LDS_PEAK_GBS = 256 * 128 * 2.4e9 / 1e9
 
@@ -557,8 +560,8 @@ def main():
             "unit": "TOP/s",
             "frac": round(achieved_tops / ALU_PEAK_TOPS, 4),
             "traffic": traffic_b,
-            "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE x2 + WRITE_SIZE x1)",
-            "kernel": "k_eval",
+            "traffic_unit": "bytes per call (rocprofv3 FETCH_SIZE x2 + WRITE_SIZE x1)",
+            "kernel": "k_eval, and k_eval_split for the rest after its whole rounds",
             "ops_per_gadget": ops_g,
         },
         "hbm": {
@@ -578,10 +581,11 @@ def main():
             "frac": round(lds_g * n / (ms_step / 1e3) / 1e9 / LDS_PEAK_GBS, 4),
             "bytes_per_gadget": lds_g,
         },
-        # measured VALU issue: SQ_INSTS_VALU x 4 cycles per wave64 instruction on a 16-lane SIMD,
-        # against 1,024 SIMDs x 2.4 GHz over the launch (None once the kernel changed)
-        "valu_issue": {"instructions_per_launch": valu_i,
-                       "frac": None if valu_i is None else round(valu_i * 4 / (1024 * 2.4e9 * ms_step / 1e3), 4),
+        # measured vector instructions of a call (SQ_INSTS_VALU) at 2 and at 4 cycles each, the two
+        # costs there are, against 1,024 SIMDs x 2.4 GHz over the call (None once the kernels changed)
+        "valu_issue": {"instructions_per_call": valu_i,
+                       "frac_at_2_cycles": None if valu_i is None else round(valu_i * 2 / (1024 * 2.4e9 * ms_step / 1e3), 4),
+                       "frac_at_4_cycles": None if valu_i is None else round(valu_i * 4 / (1024 * 2.4e9 * ms_step / 1e3), 4),
                        "source": "rocprofv3 SQ_INSTS_VALU"},
         "aes_blocks_per_s": round(aes_g * gadgets_per_s, 1),
         "aes_roofline": {"achieved": round(aes_g * gadgets_per_s, 1), "peak": round(aes_peak, 1),

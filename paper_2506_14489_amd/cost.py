@@ -18,6 +18,12 @@ Per gadget (structure of the gate list in include/redash.h):
       - per output residue (m > 2): 14 (digit split 3, row add 3, free
         operation 5, field extract and insert 3); per word for m = 2: 3;
   * LDS table reads: 160 4-byte lookups per AES block (T-table AES).
+
+The model counts the table formulation in full.  The kernels do less: the two
+blocks of a hash share lookups of their first rounds and a pad is taken from
+the leading limbs (281 lookups of 320 per hash, 17 to 22 limb products of 40
+to 48 per pad), and one instruction (a three-input XOR, a byte permute, a
+multiply-add with a table's address) does several modelled operations.
 """
 
 from __future__ import annotations
