@@ -12,25 +12,28 @@
 //     enters as v - 128 (v XOR 0x80), and adding 128 * sum_k w (the row sums,
 //     prepared with the weights) restores sum w v exactly.
 //
-// Two kernels per call:
+// Two kernels per call, as the host plan (linear_plan.cpp) says:
 //   k_linear_unpack  reads the packed input labels once and writes every
-//                    residue as a byte into residue planes in the caller's
-//                    working buffer: plane (i, r) holds residue r of modulus
-//                    i for every input position, channel-last with the zero
-//                    padding already in place, so that a 16-byte load gives a
-//                    matrix-core fragment of 16 channels (HBM-bound);
-//   k_linear_gemm_w  (one channel chunk) per workgroup: one modulus and 64
-//                    output channels, the weights staged in LDS once; each
-//                    wave then takes its own row segment of XT (32 or 16)
-//                    output positions, 4 x (XT/16) MFMA 16x16x64 tiles, and
-//                    runs through every residue of the modulus with its own
-//                    staged input halo, reducing the int32 sums mod m into
-//                    PK32 fields and storing each packed word whole;
-//   k_linear_gemm    (several channel chunks) per workgroup: one modulus, 64
-//                    output channels and a row segment; wave q takes residue
-//                    j0 + q of each packed word, the halos and the weights of
-//                    each chunk staged by the workgroup, the residues of a
-//                    word merged across the waves in LDS.
+//                    residue as a byte (or a field of one, for the small
+//                    moduli) into residue planes in the caller's working
+//                    buffer, one plane per residue for every input position,
+//                    channel-last with the zero padding already in place, so
+//                    that a 16-byte load gives a matrix-core fragment of 16
+//                    channels (HBM-bound); k_linear_unpack_rows does so for a
+//                    layer of few channels, without gaps between positions;
+//   k_linear_gemm_w  (one channel chunk) per workgroup: one modulus (or packed
+//                    word) and 64 output channels, the weights staged in LDS
+//                    once; each wave then takes its own row segment of XT (32
+//                    or 16) output positions, 4 x (XT/16) MFMA 16x16x64 tiles,
+//                    and runs through every residue with its own staged input
+//                    halo, reducing the int32 sums mod m into PK32 fields and
+//                    storing each packed word whole;
+//   k_linear_gemm    (several channel chunks) per workgroup: one modulus (or
+//                    packed word), 64 output channels and a tile of a row or of
+//                    the flattened plane; wave q takes residue j0 + q of each
+//                    packed word, the halos and the weights of each chunk staged
+//                    by the workgroup, the residues of a word merged across the
+//                    waves in LDS.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -1,11 +1,14 @@
 // Kernels and C ABI of the ReDASH scaling-gadget library for gfx950.
 //
-// One thread evaluates (or garbles) one gadget instance.  Labels are packed
-// words laid out [word][gadget], so a wavefront's label accesses are 64
-// consecutive words; the gate list and all per-modulus constants are uniform
-// and come from the kernel argument block (scalar registers).  The AES round
-// tables are staged into LDS once per workgroup.  Nothing here uses MFMA: the work is table lookups, XORs, 32-bit
-// multiplies for digit extraction and small modular arithmetic.
+// A large call evaluates one gadget per lane (k_eval); smaller ones spread a
+// gadget's gates over waves (k_eval_split, k_garble) or over lanes
+// (k_eval_small), encode and decode its moduli over workgroups and waves.
+// Labels are packed words laid out [word][gadget], so a wavefront's label
+// accesses are 64 consecutive words; the gate list and all per-modulus
+// constants are uniform and come from the kernel argument block (scalar
+// registers).  The AES round tables are staged into LDS once per workgroup.
+// Nothing here uses MFMA: the work is table lookups, XORs, 32-bit multiplies
+// for digit extraction and small modular arithmetic.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
@@ -27,10 +30,13 @@ struct SeedKey {
 //
 // LDS of a workgroup (addresses from 0: the kernel declares no static LDS):
 // the 64 KiB two-table image, the 88 round-key words, then one 128-byte
-// free-operation table per gate (up to kMaxTables).  The working labels stay in global memory, mostly in L2: the
-// output tensor (and the working storage for Phase-B copies) holds every
-// intermediate label, each gate reads its destination label and its table
-// row before the AES runs and writes the destination back after it.
+// free-operation table per gate (up to kMaxTables).  k_eval keeps a block's two
+// target labels in registers from their first gate to their last; the other
+// labels it reads are in global memory, mostly in L2 (the input, the output
+// tensor, the working storage for Phase-B copies).  k_eval_split reads a gate's
+// destination label and row there before the hash and writes the label back
+// after it.  k_eval_small keeps every label of its gadgets in LDS, behind the
+// tables.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kEvalTableBase = kTableRegionBytes + 384;  // after the 352 key bytes
 // LDS bytes of an evaluator workgroup with ntab free-operation tables.
