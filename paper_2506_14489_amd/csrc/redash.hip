@@ -184,26 +184,21 @@ __device__ __forceinline__ void fold_regs(const uint32_t (&T)[kMaxW], uint32_t (
 // Moduli without the fast constants (4 and 16, whose fields fill a word, and
 // the primes 41, 47, 53, 59 and 61, whose split parts are too large for the
 // 24-bit digit steps): one residue at a time with 32-bit divisions, over all
-// kMaxW positions in a rolled loop that rotates the label and the row (and with
-// WORDS the pad) by one word per position (kMaxW rotations put label and row
-// back in place).  Without WORDS a word of the pad is taken from the hash
-// fraction V as it is needed.  The gadget configurations in use all take the
-// fast path.
-template <bool WORDS>
-__device__ __forceinline__ void reg_update_generic(uint32_t e, const ModConst &mm, uint32_t (&V)[8],
-                                                   uint32_t (&Dw)[kMaxW], uint32_t (&row)[kMaxW],
-                                                   uint32_t (&T)[kMaxW]) {
+// kMaxW positions in a rolled loop that rotates the label, the row and the pad
+// by one word per position (kMaxW rotations put label and row back in place).  The gadget
+// configurations in use all take the fast path.
+__device__ __forceinline__ void reg_update_generic(uint32_t e, const ModConst &mm, uint32_t (&Dw)[kMaxW],
+                                                   uint32_t (&row)[kMaxW], uint32_t (&T)[kMaxW]) {
     const uint32_t coeff = eg_coeff(e), off = label_off(mm);
 #pragma unroll 1
     for (uint32_t p = 0; p < static_cast<uint32_t>(kMaxW); ++p) {
         const uint32_t l = next_word(T);
         const uint32_t rw = next_word(row);
-        uint32_t D = WORDS ? next_word(Dw) : 0u;
+        uint32_t D = next_word(Dw);
         uint32_t res = l;
         if (p >= off) {
             const bool last = (p + 1 == static_cast<uint32_t>(kMaxW));
             const uint32_t nres = last ? mm.glast : mm.g;
-            if constexpr (!WORDS) D = frac_carry_any(V, last ? mm.pw_last : mm.pw_g);
             res = 0;
             for (uint32_t j = nres; j-- > 0;) {
                 uint32_t pd;
@@ -280,11 +275,9 @@ __device__ __forceinline__ void reg_update_fast(uint32_t e, const ModConst &mm, 
 // rns_to_mrs) or L <- L + c E (acc: the mixed-radix recombination onto a
 // scaling modulus).  For an output modulus m <= 42 the products c' y mod m
 // (fast_word) come from the gate's byte table in LDS.
-// D: the gate's pad (pad_words_top, pad_words_all); V: its hash fraction, for
-// the moduli without the fast constants (gate_pad with WORDS false).
-template <bool WORDS>
-__device__ __forceinline__ void reg_update(uint32_t g, uint32_t e, const ModConst &mm, uint32_t (&V)[8],
-                                           uint32_t (&D)[kMaxW], uint32_t (&row)[kMaxW], uint32_t (&T)[kMaxW]) {
+// D: the gate's pad (pad_words_top, pad_words_all).
+__device__ __forceinline__ void reg_update(uint32_t g, uint32_t e, const ModConst &mm, uint32_t (&D)[kMaxW],
+                                           uint32_t (&row)[kMaxW], uint32_t (&T)[kMaxW]) {
     if (mm.m == 2) {  // W = 4: positions 2..5
         const bool flip = eg_kind(e) == 0 || (eg_coeff(e) & 1u);  // sub: q^{-1} = 1 mod 2
         if (flip) {
@@ -295,7 +288,7 @@ __device__ __forceinline__ void reg_update(uint32_t g, uint32_t e, const ModCons
     } else if (mm.fast) {
         reg_update_fast<false>(e, mm, D, row, T, 0);
     } else {
-        reg_update_generic<WORDS>(e, mm, V, D, row, T);
+        reg_update_generic(e, mm, D, row, T);
     }
 }
 
@@ -316,11 +309,7 @@ __device__ __forceinline__ void stage_free_op_tables_e(const EvalPlan &P, uint32
 // lane's digits could depend on limbs 0-2 (about once in 2^12 waves) the
 // wave hashes the gate's first block again for them: digit(x) reads and folds
 // the digit label, tau() is the tweak.
-// WORDS false (the split evaluator): the moduli without the fast constants keep
-// V and D is not set, the update then takes each word as it comes to it (base
-// (4, 47, 53, 59), 100,000 gadgets: 96.7 -> 95.5 us; k_eval has no registers for
-// V there: 28 bytes of scratch).
-template <bool WORDS, typename Digit, typename Tau>
+template <typename Digit, typename Tau>
 __device__ __forceinline__ void gate_pad(const PermTE02 &TT, const uint32_t *K, uint32_t gid, const ModConst &mm,
                                          uint32_t (&V)[8], uint32_t (&D)[kMaxW], Digit &&digit, Tau &&tau) {
     if (mm.pad_amb != 0) {
@@ -335,7 +324,7 @@ __device__ __forceinline__ void gate_pad(const PermTE02 &TT, const uint32_t *K, 
         V[6] = v6;
         V[7] = v7;
     }
-    if (WORDS || mm.fast || mm.m == 2) pad_words_all(V, mm, D);
+    pad_words_all(V, mm, D);
 }
 
 // The gadget index a (below 2^30) is a 32-bit value: the row offset
@@ -432,9 +421,8 @@ k_eval(const EvalPlan P, const uint32_t *__restrict__ in, const uint32_t *__rest
                 // registers through the hash)
                 asm volatile("" : "+s"(e));
                 const ModConst mm = P.mod[eg_dst(e)];
-                gate_pad<true>(TT, K, P.gid, mm, V, D, digit,
-                               [&] { return gate_tweak(P, opaque(LB.aoff) >> 2, g + j); });
-                reg_update<true>(g + j, e, mm, V, D, row, T[0]);
+                gate_pad(TT, K, P.gid, mm, V, D, digit, [&] { return gate_tweak(P, opaque(LB.aoff) >> 2, g + j); });
+                reg_update(g + j, e, mm, D, row, T[0]);
                 if (two) swap_slots(T);
             }
             if (alone1) swap_slots(T);
@@ -528,11 +516,11 @@ k_eval_split(const SplitPlan P, const uint32_t *__restrict__ in, const uint32_t 
             load_label(T, LB, gate_tsrc(d), mm, gate_tsrc(d) != kLocZero);
             uint32_t V[8], D[kMaxW];
             hash_pair(TT, LdsKey{K}, x, [&] { return opaque64(tau0 + g + i); }, P.gid, mm.pad_amb == 0, V);
-            gate_pad<false>(TT, K, P.gid, mm, V, D,
-                            [&](uint32_t(&f)[4]) { static_for<4>([&](auto l) { f[l] = x[l]; }); },
-                            [&] { return tau0 + g + i; });
+            gate_pad(TT, K, P.gid, mm, V, D,
+                     [&](uint32_t(&f)[4]) { static_for<4>([&](auto l) { f[l] = x[l]; }); },
+                     [&] { return tau0 + g + i; });
             const uint32_t e = gate_dst(d) | (gate_kind(d) << 4) | (gate_tab(d) << 5) | (gate_coeff(d) << 6);
-            reg_update<false>(g + i, e, mm, V, D, row, T);
+            reg_update(g + i, e, mm, D, row, T);
             store_label(T, LB, gate_tdst(d), mm);
         }
         __syncthreads();
@@ -684,8 +672,8 @@ k_eval_small(const SplitPlan P, const uint32_t *__restrict__ in, const uint32_t 
                 if (w < mm.W) {
                     uint32_t V[8], D[kMaxW];
                     static_for<8>([&](auto l) { V[l] = Vb[l * (r * c) + i * c + gl]; });
-                    gate_pad<true>(TT, K, P.gid, mm, V, D, [&](uint32_t(&x)[4]) { digit(gl, x); },
-                                   [&] { return (P.a0 + a0 + gl) * P.G + g + i; });
+                    gate_pad(TT, K, P.gid, mm, V, D, [&](uint32_t(&x)[4]) { digit(gl, x); },
+                             [&] { return (P.a0 + a0 + gl) * P.G + g + i; });
                     const uint32_t at = w + label_off(mm);
                     uint32_t Dw = 0;
                     static_for<kMaxW>([&](auto p) { Dw = at == static_cast<uint32_t>(p) ? D[p] : Dw; });
@@ -926,8 +914,7 @@ k_garble(const Plan P, const SeedKey key, const uint32_t *__restrict__ offsets, 
             hash_pair(TT, HK, x, tweak, P.gid, P.mod[gate_dst(dc)].pad_amb == 0, V);
             asm volatile("" : "+s"(dc));
             const ModConst mm = P.mod[gate_dst(dc)];
-            gate_pad<true>(
-                TT, K, P.gid, mm, V, D, [&](uint32_t(&f)[4]) { fold_label(A, P.mod[gate_src(dc)], f); }, tweak);
+            gate_pad(TT, K, P.gid, mm, V, D, [&](uint32_t(&f)[4]) { fold_label(A, P.mod[gate_src(dc)], f); }, tweak);
             pack_pad(D, mm);
             if (c != 0) {
                 // colours 1..q-1: the row B_c - H(A_{v_c})
