@@ -31,10 +31,10 @@ WRITE_FACTOR = 1048576 / 1048576
 MEASURED = {
     "batched": {
         "kernel": "k_eval",
-        "fetch_kib": 12694023.0 + 279418.0,  # means of four calls, within 50 KiB
-        "write_kib": 1376256.0 + 98459.0,
-        "valu_insts": 3350448532 + 71759275,  # SQ_INSTS_VALU (wave instructions; two calls, equal)
-        "sources_sha256": "fe8b6fe42bc8825ce3179c18fcc59465ca89ab1d76b6cd0543b37f6f70eebd32",
+        "fetch_kib": 12693988.0 + 279081.0,  # means of four calls, within 50 KiB
+        "write_kib": 1376256.0 + 98529.0,
+        "valu_insts": 3346025062 + 70022396,  # SQ_INSTS_VALU (wave instructions; two calls, equal)
+        "sources_sha256": "fff0dca832ca7ae83231d6af31f1aa3d5b06d759a472a560729b3ef9ae36e13d",
     },
 }
 
